@@ -260,12 +260,15 @@ int nqs_sync(nqs_ham h, void *hip_stream);
 /*
  * Counters of the last nqs_eloc_eval on this handle (valid after nqs_sync):
  *   out[0] pairs      = n * G (sample, group) pair-evaluations
- *   out[1] probes     = pairs that passed the sector test (lookups of x')
+ *   out[1] probes     = pairs that passed the sector test (lookups of x');
+ *                       with the pair join or the comparison of all pairs,
+ *                       the ordered pairs of samples within the largest flip
  *   out[2] hits       = lookups that found x' in S (off-diagonal)
  *   out[3] terms      = Pauli terms evaluated (diagonal group plus hit groups)
  *   out[4] candidates = lookups that passed the on-chip filter and went to
  *                       the hash table in device memory (with the pair
- *                       join: the ordered pairs of samples sharing a group)
+ *                       join: the ordered pairs of samples sharing a group;
+ *                       when all pairs are compared: n (n - 1))
  *   out[5] rounds     = sample rounds run by the flip enumeration (0 when
  *                       the group-streaming kernel did the lookups)
  * With the enumeration, probes counts every spin-conserving single and
@@ -279,7 +282,8 @@ int nqs_eval_stats(nqs_ham h, int64_t out[6]);
  * handle; out[0..6] are host-side and valid as soon as the call has
  * returned, out[7] after nqs_sync:
  *   out[0] strategy planned besides the pair join: NQS_STRATEGY_STREAM or
- *          NQS_STRATEGY_ENUM
+ *          NQS_STRATEGY_ENUM (under AUTO the comparison of all pairs may
+ *          stand in its place: out[0..3] then describe what it replaces)
  *   out[1] filter partitions (sample classes) of the enumeration filter:
  *          1, 2, 4 or 8 (0 when streaming is planned)
  *   out[2] 32-bit words per enumeration filter partition
@@ -288,7 +292,8 @@ int nqs_eval_stats(nqs_ham h, int64_t out[6]);
  *   out[5] 32-bit words of the streaming kernel's Bloom bitmap
  *   out[6] qubit blocks of the pair join, 0 when no join was launched
  *   out[7] whether the device ran the pair join: 1, 0, or -1 (not launched)
- * Which of the others ran is in nqs_eval_stats (rounds > 0: enumeration).
+ * Which of the others ran is in nqs_eval_stats (rounds > 0: enumeration;
+ * candidates = n (n - 1): all pairs).
  * Errors: NQS_E_STATE (bad handle, nothing evaluated yet), NQS_E_ARG,
  * NQS_E_DEVICE.
  */
@@ -383,11 +388,15 @@ int nqs_debug_dump(nqs_ham h, int64_t n, const uint64_t *samples, const double *
  *     the bucket keys; about two thousand entries each on average);
  *     otherwise (decided on the device) the enumeration or streaming
  *     strategy runs instead.
- *   NQS_STRATEGY_AUTO (0): the pair join is launched beside the enumeration
- *     (where the table allows it) or streaming, and the device runs the
- *     join when its counted cost (sum of squared group sizes plus a term
- *     per entry) is below the other strategy's (the
- *     enumeration's lookups, or half the sample-group pairs of streaming).
+ *   NQS_STRATEGY_AUTO (0): where comparing all pairs of samples on the
+ *     matrix cores takes less time than the enumeration (where the table
+ *     allows it) or streaming would, as estimated from n and the table, it
+ *     takes their place; batches of up to 8192 samples, and tables without
+ *     a pair join, then run it alone.  Otherwise the pair join is launched
+ *     beside the one or the other, and the device runs the join when its
+ *     counted cost (the sum of squared group sizes, a term per entry, and
+ *     beside the comparison of all pairs its largest group) is below the
+ *     other strategy's.
  *     Batches (nqs_batch_*) make the same decision per job: a job's
  *     grouping and pair kernels are launched around the persistent
  *     kernels, which skip the job when its device chose the join.  Served

@@ -15,8 +15,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnqs.so")
 
-SOURCES = ["nqs_api.hip", "nqs_kernels.hip", "nqs_join.hip", "nqs_server.hip", "nqs_table.cpp",
-           "nqs_host.cpp"]
+SOURCES = ["nqs_api.hip", "nqs_kernels.hip", "nqs_join.hip", "nqs_pairs.hip",
+           "nqs_server.hip", "nqs_table.cpp", "nqs_host.cpp"]
 # the host-only part, buildable without the device code (sanitizer test)
 HOST_SOURCES = ["nqs_table.cpp", "nqs_host.cpp"]
 

@@ -50,6 +50,7 @@ constexpr size_t kSeqOffset = kErrOffset + 8;  // the device's copy of it (in sm
 constexpr size_t kEnergyHostBytes = kEnergyHostOut + 4 * sizeof(double);
 constexpr size_t kMaxFilterWords = size_t(1) << 15;  // 128 KB Bloom bitmap
 constexpr size_t kMaxEFilterWords = kMaxFilterWords * nqs::kEnumMaxParts;
+constexpr uint64_t kMinSlots = 128;  // of the sample hash
 constexpr int64_t kMaxGroups = int64_t(1) << 26;     // queue entries pack the group in 26 bits
 
 }  // namespace
@@ -147,6 +148,15 @@ nqs::DevScratch scratch_of(nqs_ham h) {
     return s;
 }
 
+// The comparison of all pairs, its scratch in the space of the sample hash
+// (kMinSlots or 4 n slots hold it: 32 or 64 bytes of operand and a 32-byte
+// record per sample, against 64 or 96 bytes of slots).
+void set_pairs(nqs::DevScratch *s, nqs_ham h, const nqs::EvalLaunch &L, char *slots) {
+    s->pairs = L.pairs;
+    s->pairs_split = L.pairs_split;
+    if (L.pairs) nqs::pairs_scratch_layout(h->dt, L.n, slots, s);
+}
+
 // Filter sizes of one evaluation plan.
 void set_filters(nqs::DevScratch *s, nqs_ham h, const nqs::EvalLaunch &L) {
     s->filter_log2 = L.filter_log2;
@@ -157,18 +167,19 @@ void set_filters(nqs::DevScratch *s, nqs_ham h, const nqs::EvalLaunch &L) {
         nqs::join_scratch_layout(h->dt, L.n, L.join_log2m, static_cast<char *>(h->jmem), s);
         s->join_force = L.join_force;
     }
+    set_pairs(s, h, L, static_cast<char *>(h->slots));
 }
 
 // Partial-sum slots per sample a plan needs: its group chunks, or one per
 // join block when the pair join may run.
 int64_t plan_chunks(const nqs_ham h, const nqs::EvalLaunch &L) {
     const int64_t c = L.n_chunks > 0 ? L.n_chunks : 1;
-    return L.join ? std::max<int64_t>(c, h->dt.join_blocks) : c;
+    return L.join_scratch ? std::max<int64_t>(c, h->dt.join_blocks) : c;
 }
 
 // Bytes of the pair join's scratch for a plan (0: none planned).
 size_t plan_join_bytes(const nqs_ham h, const nqs::EvalLaunch &L) {
-    return L.join ? nqs::join_scratch_bytes(h->dt, L.n, L.join_log2m) : 0;
+    return L.join_scratch ? nqs::join_scratch_bytes(h->dt, L.n, L.join_log2m) : 0;
 }
 
 // Grow the per-handle scratch to hold a batch of n samples (and the
@@ -227,7 +238,7 @@ int regrow(T **buf, C *cap, C new_cap, size_t bytes, const char *what) {
 
 int ensure_scratch(nqs_ham h, int64_t n, int64_t n_chunks, hipStream_t st,
                    bool efilter = false, size_t join_bytes = 0) {
-    uint64_t want = 64;
+    uint64_t want = kMinSlots;
     while (want < nqs::kSlotsPerSample * static_cast<uint64_t>(n)) want <<= 1;
     if (want > (1ull << 31)) return fail(NQS_E_ARG, "batch too large for the sample hash");
     // key + index + fingerprint
@@ -287,10 +298,10 @@ int ensure_scratch(nqs_ham h, int64_t n, int64_t n_chunks, hipStream_t st,
 // Whether the scratch a plan needs is all present (a failed growth leaves
 // a buffer empty; nothing may be launched over it).
 int scratch_ready(nqs_ham h, const nqs::EvalLaunch &L) {
-    const bool ok = h->slots && h->slot_cap >= 64 && h->shx && h->part && h->filter && h->small &&
+    const bool ok = h->slots && h->slot_cap >= kMinSlots && h->shx && h->part && h->filter && h->small &&
                     (L.eparts_log2 == 0 || h->efilter) &&
                     (L.strategy != nqs::kStrategyEnum || !h->dt.enum_ok || h->eblk) &&
-                    (!L.join || (h->jmem && h->jmem_bytes >= plan_join_bytes(h, L))) &&
+                    (!L.join_scratch || (h->jmem && h->jmem_bytes >= plan_join_bytes(h, L))) &&
                     h->part_cap >= 2 * L.n * plan_chunks(h, L);
     return ok ? NQS_OK : fail(NQS_E_STATE, "scratch buffers missing after a failed allocation");
 }
@@ -312,6 +323,7 @@ struct EvalKey {
     const void *slots, *shx, *part, *filter, *efilter, *small, *eblk, *jmem;
     uint32_t slot_cap;
     int energy, join_only;
+    int pairs, pairs_split;
     const void *epart, *ehost;
 };
 static_assert(sizeof(EvalKey) <= sizeof(nqs_ham_s::eval_key), "key fits");
@@ -325,8 +337,8 @@ hipError_t issue_eval(nqs_ham h, const nqs::DevScratch &sc, const nqs::EvalLaunc
     hipError_t e;
     const bool prof = h->profiling && may_profile;
     if (prof && (e = hipEventRecord(h->ev[0], s)) != hipSuccess) return e;
-    if ((e = nqs::launch_hash(h->dt, sc, sc.slot_mask + 1u, samples, weights, n, s,
-                              prof ? h->ev[4] : nullptr, L.join_only != 0)) != hipSuccess)
+    if ((e = nqs::launch_hash(h->dt, sc, sc.slot_mask + 1u, samples, weights, log_amp, phase, n,
+                              s, prof ? h->ev[4] : nullptr, L.join_only != 0)) != hipSuccess)
         return e;
     if (prof && (e = hipEventRecord(h->ev[1], s)) != hipSuccess) return e;
     const int64_t sign_words = (h->dt.n_terms + 31) / 32;
@@ -409,6 +421,7 @@ int eval_impl(nqs_ham h, int64_t n, const uint64_t *samples, const int64_t *weig
     nqs::EvalLaunch L = nqs::plan_eval(h->dt, n, dump, &h->tune);
     // (only where a join is launched and may be chosen)
     L.join_only = join_only && L.join && !dump ? 1 : 0;
+    if (L.join_only) L.pairs = 0;
     int rc = ensure_scratch(h, n, plan_chunks(h, L), st, L.eparts_log2 > 0, plan_join_bytes(h, L));
     if (!rc) rc = scratch_ready(h, L);
     if (rc) return rc;
@@ -450,6 +463,8 @@ int eval_impl(nqs_ham h, int64_t n, const uint64_t *samples, const int64_t *weig
         key.slot_cap = h->slot_cap;
         key.energy = energy ? 1 : 0;
         key.join_only = L.join_only;
+        key.pairs = L.pairs;
+        key.pairs_split = L.pairs_split;
         key.epart = energy ? h->epart : nullptr;
         key.ehost = energy ? h->ehost : nullptr;
         const bool same = h->have_key && std::memcmp(h->eval_key, &key, sizeof key) == 0;
@@ -525,7 +540,7 @@ int noalloc_base(int dev, char **out) {
 size_t layout_scratch(nqs_ham h, const nqs::EvalLaunch &L, int64_t n, int n_cu, char *base,
                       size_t cap, nqs::DevScratch *sc, void *small = nullptr) {
     if (!small) small = h->small;
-    uint64_t slots = 64;
+    uint64_t slots = kMinSlots;
     while (slots < nqs::kSlotsPerSample * static_cast<uint64_t>(n)) slots <<= 1;
     const int64_t chunks = plan_chunks(h, L);
     const size_t sizes[7] = {
@@ -562,6 +577,7 @@ size_t layout_scratch(nqs_ham h, const nqs::EvalLaunch &L, int64_t n, int n_cu, 
         nqs::join_scratch_layout(h->dt, n, L.join_log2m, base + off[6], sc);
         sc->join_force = L.join_force;
     }
+    set_pairs(sc, h, L, base + off[0]);
     return total;
 }
 
@@ -748,6 +764,19 @@ int create_handle(nqs_ham *out, const nqs::HostTable &T, const std::vector<doubl
         const int q0 = b * T.n_qubits / d.join_blocks, q1 = (b + 1) * T.n_qubits / d.join_blocks;
         for (int q = q0; q < q1; ++q) d.jmask[b][q >> 6] |= 1ull << (q & 63);
     }
+    double near = 0.0, choose = 1.0;
+    for (int k = 0; k <= T.max_flip && k <= T.n_qubits; ++k) {
+        near += choose;
+        choose = choose * (T.n_qubits - k) / (k + 1);
+    }
+    d.near_share = std::ldexp(near, -T.n_qubits);
+    const auto two = [](double m) { return 0.5 * m * (m - 1.0); };
+    const double ka = T.k_alpha, kb = T.k_beta, na = T.k_alpha / 2, nb = T.k_beta / 2;
+    const double sa = na * (ka - na), sb = nb * (kb - nb);
+    d.half_flips = sa + sb + sa * sb + two(na) * two(ka - na) + two(nb) * two(kb - nb);
+    d.half_states = 1.0;
+    for (int k = 1; k <= T.k_alpha / 2; ++k) d.half_states *= (ka - na + k) / k;
+    for (int k = 1; k <= T.k_beta / 2; ++k) d.half_states *= (kb - nb + k) / k;
     d.diag_occ = T.diag_occ ? 1 : 0;
     d.diag = T.diag_occ ? reinterpret_cast<const double *>(base + pieces[13].off) : nullptr;
     d.diag32 = T.diag_occ ? reinterpret_cast<const float *>(base + pieces[14].off) : nullptr;
@@ -1515,7 +1544,7 @@ int plan_batch(const nqs_batch_item *items, int n_items, int threads, hipStream_
         // enumeration rounds assume 1024-thread blocks
         if (th != kEnumThreads) t.strategy = kStrategyStream;
         EvalLaunch L = plan_eval(h->dt, std::max<int64_t>(it.n, 1), false, &t);
-        if (it.n == 0) L.join = 0;
+        if (it.n == 0) L.join = L.pairs = 0;
         if (L.strategy == kStrategyEnum && L.chunk_len > 0) {
             // the streaming items are only a fallback here (mixed sectors):
             // one group chunk keeps their number small
@@ -1571,7 +1600,7 @@ int plan_batch(const nqs_batch_item *items, int n_items, int threads, hipStream_
         shape.enum_begin[v] = static_cast<int>(work.size());
         for (int k : order) {
             const JobDesc &J = jobs[k];
-            if (J.n == 0 || J.strategy != kStrategyEnum) continue;
+            if (J.n == 0 || J.strategy != kStrategyEnum || J.sc.pairs) continue;
             const int jv = (J.kind & 1) + ((J.kind & kJobIntegrals) ? 2 : 0);
             if (jv != v) continue;
             const int64_t S = std::min<int64_t>((J.n + 63) / 64, int64_t(1) << 20);
@@ -1582,7 +1611,7 @@ int plan_batch(const nqs_batch_item *items, int n_items, int threads, hipStream_
     shape.enum_begin[kEnumVariants] = static_cast<int>(work.size());
     for (int k : order) {
         const JobDesc &J = jobs[k];
-        if (J.n == 0 || J.chunk_len == 0) continue;
+        if (J.n == 0 || J.chunk_len == 0 || J.sc.pairs) continue;
         const int64_t tiles = (J.n + th - 1) / th;
         for (int64_t c = 0; c < J.n_chunks; ++c)
             for (int64_t t = 0; t < tiles; ++t)

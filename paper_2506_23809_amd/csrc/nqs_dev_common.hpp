@@ -422,6 +422,25 @@ __device__ __forceinline__ int64_t group_find(const DevTable &tab, uint32_t hX, 
     return -1;
 }
 
+// Sum of FP64 values as an unevaluated pair hi + lo: the rounding errors of
+// the additions (TwoSum) go to lo, so the value, rounded once, does not
+// depend on the order of the additions (up to ties closer than about 2^-100
+// of the largest partial sum).  An infinity or NaN passes through hi.
+struct Acc2 {
+    double hi = 0.0, lo = 0.0;
+    __device__ __forceinline__ void add(double v) {
+        const double s = hi + v, bp = s - hi;
+        lo += (hi - (s - bp)) + (v - bp);
+        hi = s;
+    }
+    // another sum (its lo counts only beside a finite hi)
+    __device__ __forceinline__ void add(double vhi, double vlo) {
+        add(vhi);
+        if (isfinite(vhi)) add(vlo);
+    }
+    __device__ __forceinline__ double value() const { return isfinite(hi) ? hi + lo : hi; }
+};
+
 // ------------------------------------------------------------------ hash build
 
 // One thread per sample: range check, sector uniformity, counts >= 0, linear

@@ -69,6 +69,11 @@ struct DevTable {
     int max_flip;          // largest popc(X) over the groups
     int join_blocks;       // max_flip + 1, or 0 when that exceeds kJoinMaxBlocks
     uint64_t jmask[kJoinMaxBlocks][2];
+    // for the choice between comparing all pairs and the other strategies:
+    // the share of random pairs of bit strings within max_flip, and the
+    // spin-conserving singles and doubles of a half-filled sample and the
+    // states of its sector
+    double near_share, half_flips, half_states;
 };
 
 // ---- flip enumeration: shape of one round
@@ -211,7 +216,7 @@ struct DevScratch {
                                 // of two or more)
     uint32_t *jhit;             // [ceil(blocks * n / 32)] bit b * n + i: entry (b, i) has a
                                 // hit and wrote its partial
-    unsigned long long *jstat;  // [parts][2] sum of squared group sizes, largest bucket
+    unsigned long long *jstat;  // [parts][2] sum of squared group sizes, largest group
     unsigned long long *jctl;   // [kJoinCtl] see kJoinCtl*
     int join_log2m;
     int64_t join_n;             // samples of the launch (the partials' row length)
@@ -221,10 +226,18 @@ struct DevScratch {
     int join_tiles;
     int join_cap;               // entries of a partition's region
     int join_force;             // 1: join whenever it can run, 0: when cheaper
+    // comparison of all pairs: 0 none, 1 for this launch, 2 unless the device
+    // chose the pair join; its operands and records (in the space of the
+    // sample hash, which such a launch does not build), and the shares the
+    // samples y are split into (one partial each)
+    int pairs;
+    int pairs_split;
+    char *pops;
+    char *prec;
 };
 
 // Pair-join control words (jctl): the enumeration's probe count, the join's
-// ordered candidate pairs (sum of squared group sizes), the largest bucket,
+// ordered candidate pairs (sum of squared group sizes), the largest group,
 // whether a partition exceeded kJoinPartCap, and the decision (1: the join
 // runs); then 64 slots of the probe count.
 enum { kJoinCtlProbes = 0, kJoinCtlCost = 1, kJoinCtlMax = 2, kJoinCtlOver = 3,
@@ -239,6 +252,11 @@ constexpr int64_t kJoinMaxSamples = int64_t(1) << 21;
 // Whether the pair join was chosen for this launch (device side).
 __device__ __forceinline__ bool join_chosen(const DevScratch &sc) {
     return sc.jctl != nullptr && sc.jctl[kJoinCtlChosen] != 0ull;
+}
+
+// Whether this launch compares all pairs of samples (device side).
+__device__ __forceinline__ bool pairs_chosen(const DevScratch &sc) {
+    return sc.pairs == 1 || (sc.pairs == 2 && !join_chosen(sc));
 }
 
 constexpr uint32_t kGoldenMul = 0x9E3779B1u;
@@ -280,6 +298,13 @@ struct EvalLaunch {
     // launch); its result is valid only if the device chose the join, which
     // the caller checks (nqs_eloc_energy, after its previous call chose it)
     int join_only;
+    // comparison of all pairs of samples instead of the enumeration or
+    // streaming (DevScratch::pairs), and the shares of its columns
+    int pairs;
+    int pairs_split;
+    // 1: the scratch holds the pair join's arrays (also where all pairs are
+    // compared without it: the space a handle takes follows from n alone)
+    int join_scratch;
 };
 
 // Bytes of the pair join's scratch for n samples and the table's blocks
@@ -305,6 +330,17 @@ hipError_t launch_join_pairs(const DevTable &tab, const DevScratch &sc, const ui
                              const double *phase, int64_t n, int precision, int32_t *hit_idx,
                              uint32_t *sign_bits, int64_t sign_words, hipStream_t st);
 
+// The comparison of all pairs: scratch, the launch that clears the counters,
+// checks the samples and lays them out, and the pair kernel.
+size_t pairs_scratch_bytes(const DevTable &tab, int64_t n);
+void pairs_scratch_layout(const DevTable &tab, int64_t n, char *base, DevScratch *sc);
+hipError_t launch_pairs_prep(const DevTable &tab, const DevScratch &sc, const uint64_t *samples,
+                             const int64_t *weights, const double *log_amp, const double *phase,
+                             int64_t n, hipStream_t st);
+hipError_t launch_pairs(const DevTable &tab, const DevScratch &sc, const double *log_amp,
+                        const double *phase, int64_t n, int precision, int32_t *hit_idx,
+                        uint32_t *sign_bits, int64_t sign_words, hipStream_t st);
+
 constexpr int kStrategyAuto = 0, kStrategyStream = 1, kStrategyEnum = 2, kStrategyJoin = 3;
 
 // Optional event recorded between the lookup and the finish kernels.
@@ -329,8 +365,9 @@ EvalLaunch plan_eval(const DevTable &tab, int64_t n, bool dump, const Tuning *tu
 // With join_only (a launch of the join's kernels alone) the sample hash is
 // neither cleared nor filled: nothing reads it.
 hipError_t launch_hash(const DevTable &tab, const DevScratch &sc, uint32_t capacity,
-                       const uint64_t *samples, const int64_t *weights, int64_t n,
-                       hipStream_t st, hipEvent_t after_grouping = nullptr,
+                       const uint64_t *samples, const int64_t *weights, const double *log_amp,
+                       const double *phase, int64_t n, hipStream_t st,
+                       hipEvent_t after_grouping = nullptr,
                        bool join_only = false);
 // Eq. 1 taken beside an evaluation: the finish kernel writes one partial set
 // (sum w, sum w Re E, sum w Im E, M2 about the block mean) per block to part

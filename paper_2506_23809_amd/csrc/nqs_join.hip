@@ -355,7 +355,7 @@ __device__ __forceinline__ void join_sort_partition(const DevTable &tab, const D
     // a smaller fingerprint, then those of its own fingerprint with a smaller
     // sample index; its range is its fingerprint group (the whole bucket for
     // a bitonic-sorted partition)
-    unsigned long long pairs = 0;
+    unsigned long long pairs = 0, largest = 0;
     for (uint32_t u = threadIdx.x; u < c; u += blockDim.x) {
         const uint32_t v = buf[u];
         const uint32_t loc = v >> 21, me = v & 0x1FFFFFu;
@@ -377,6 +377,7 @@ __device__ __forceinline__ void join_sort_partition(const DevTable &tab, const D
             gm = same;
         }
         pairs += gm;
+        largest = gm > largest ? gm : largest;
         const uint32_t dst = s0 + bs + rank;
         sc.jent[dst] = me;
         sc.jrange[dst] = (s0 + gs) | (static_cast<unsigned long long>(gm) << 32) |
@@ -385,16 +386,15 @@ __device__ __forceinline__ void join_sort_partition(const DevTable &tab, const D
         if (gm >= 2) keys[dst] = src[me];
     }
     // the partition's sum of squared group sizes (each entry adds its
-    // group's size) and its largest bucket
-    unsigned long long unused = 0;
-    block_sum_max(pairs, unused);
+    // group's size) and its largest group
+    block_sum_max(pairs, largest);
     if (threadIdx.x == 0) {
         sc.jstat[2 * p] = pairs;
-        sc.jstat[2 * p + 1] = mx_all;
+        sc.jstat[2 * p + 1] = largest;
     }
 }
 
-// The join's cost and largest bucket over the partitions, and the decision
+// The join's cost and largest group over the partitions, and the decision
 // (by one whole block).
 __device__ __forceinline__ void join_decide(const DevTable &tab, const DevScratch &sc,
                                             const uint64_t *__restrict__ samples, int64_t n,
@@ -420,7 +420,7 @@ __device__ __forceinline__ void join_decide(const DevTable &tab, const DevScratc
     unsigned long long probes = 0;
     for (int k = 0; k < 64; ++k) probes += sc.jctl[kJoinCtlProbeSlots + k];
     sc.jctl[kJoinCtlProbes] = probes;
-    // costs in units of one enumeration probe, from MI355X timings of both
+    // costs in units of one enumeration probe (0.47 ps), from MI355X timings of both
     // strategies over 64 molecule-shaped jobs (24..100 qubits, 10^3..2.6 10^5
     // samples): a candidate pair of the join costs about 4 probes, an entry
     // (its grouping and its share of the pair kernel) about 40, the join's
@@ -434,7 +434,21 @@ __device__ __forceinline__ void join_decide(const DevTable &tab, const DevScratc
     const double cand = static_cast<double>(q) > entries ? static_cast<double>(q) - entries : 0.0;
     const double cost = 4.0 * cand + 40.0 * entries + 1.0e7;
     const bool fits = sc.jctl[kJoinCtlOver] == 0ull;
-    const bool chosen = fits && (sc.join_force != 0 || cost < alt);
+    bool chosen = fits && (sc.join_force != 0 || cost < alt);
+    if (sc.pairs == 2) {
+        // beside the comparison of all pairs (0.09 ps a pair and 8 us) the
+        // grouping is spent either way: what counts is the pair kernel, about
+        // two probes a candidate and 18 an entry (79 us for 86.9 M candidates
+        // at 40 qubits, 11 us for 1.3 M entries at 100), and the serial chain
+        // of its largest group, 0.1 us a member of one word and 0.7 us of
+        // two.  A call's time with the join and with all pairs: 72 and 75 us
+        // (40 qubits, 9,000 spread samples), 121 and 200 (37,843), 468 and
+        // 203 (37,843 somewhat gathered ones, 2,127 in a group), 280 and 150
+        // (100 qubits, 20,001, 307 in a group)
+        const double dn = static_cast<double>(n);
+        const double chain = (tab.n_qubits <= 63 ? 2.1e5 : 1.5e6) * static_cast<double>(m);
+        chosen = fits && 2.0 * cand + 18.0 * entries + chain < 0.19 * dn * dn + 1.7e7;
+    }
     sc.jctl[kJoinCtlCost] = q;
     sc.jctl[kJoinCtlMax] = m;
     sc.jctl[kJoinCtlChosen] = chosen ? 1ull : 0ull;
@@ -443,7 +457,7 @@ __device__ __forceinline__ void join_decide(const DevTable &tab, const DevScratc
 // One block per partition: its entries ordered by (bucket, content
 // fingerprint, sample) and written back, each with the range of its group
 // (the members of its bucket with its fingerprint), its block and its bit
-// string; the partition's sum of squared group sizes and largest bucket.  A
+// string; the partition's sum of squared group sizes and largest group.  A
 // counting sort by bucket (LDS counts, their scan, then each entry at its
 // bucket's start plus a cursor in the same word) groups the buckets; an
 // entry's place inside its bucket is then the number of members with a

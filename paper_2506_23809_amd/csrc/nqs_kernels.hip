@@ -25,6 +25,7 @@
 // the whole block.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdint>
 #include <type_traits>
 
@@ -1300,7 +1301,9 @@ __device__ __forceinline__ void enum_solo(const uint32_t *filt, const DevTable &
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 
-        double acc_re = 0.0, acc_im = 0.0;
+        // (double-double: the same bits as the comparison of all pairs
+        // gives, whatever the order of the hits)
+        Acc2 acc_re, acc_im;
         AccF32 acc_r, acc_i;
         uint32_t qn = 0;
         auto flush = [&](uint32_t mcount) {
@@ -1317,8 +1320,8 @@ __device__ __forceinline__ void enum_solo(const uint32_t *filt, const DevTable &
                 const int q = __builtin_ctzll(hm);
                 hm &= hm - 1;
                 if constexpr (P == NQS_FP64) {
-                    acc_re += readlane_f64(c.re, q);
-                    acc_im += readlane_f64(c.im, q);
+                    acc_re.add(readlane_f64(c.re, q));
+                    acc_im.add(readlane_f64(c.im, q));
                 } else {
                     acc_r.add(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(c.pre), q)),
                               __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c.ere), q)));
@@ -1384,8 +1387,8 @@ __device__ __forceinline__ void enum_solo(const uint32_t *filt, const DevTable &
         if (lane == 0) {
             double *pp = sc.part + 2 * i;
             if constexpr (P == NQS_FP64) {
-                pp[0] = acc_re;
-                pp[1] = acc_im;
+                pp[0] = acc_re.value();
+                pp[1] = acc_im.value();
             } else {
                 pp[0] = acc_r.value();
                 pp[1] = acc_i.value();
@@ -1838,8 +1841,12 @@ __device__ __forceinline__ void finish_one(const DevTable &tab, const DevScratch
                                            uint32_t *olist = nullptr, bool have_d = false,
                                            double dval = 0.0, double2 *value = nullptr) {
     unsigned long long n_terms = 0;
-    // the pair join leaves one partial per block, an enumeration one per sample
-    if (join_chosen(sc))
+    // the pair join leaves one partial per block, an enumeration and an
+    // undivided comparison of all pairs one per sample
+    const bool pairs = pairs_chosen(sc);
+    if (pairs)
+        n_chunks = sc.pairs_split == 1 ? 1 : 0;
+    else if (join_chosen(sc))
         n_chunks = tab.join_blocks;
     else if (enum_on && enum_shape(tab, sc, samples, n).B > 0)
         n_chunks = 1;
@@ -1892,7 +1899,19 @@ __device__ __forceinline__ void finish_one(const DevTable &tab, const DevScratch
                 if (hit_idx) hit_idx[i * tab.n_groups] = static_cast<int32_t>(i);
             }
         }
-        if (join_chosen(sc)) {
+        if (pairs && sc.pairs_split > 1) {
+            // all pairs in several shares: double-double partials
+            Acc2 r, m;
+            for (int s = 0; s < sc.pairs_split; ++s) {
+                const double2 *p = reinterpret_cast<const double2 *>(
+                    sc.part + 4 * (static_cast<int64_t>(s) * n + i));
+                const double2 a = p[0], b = p[1];
+                r.add(a.x, a.y);
+                m.add(b.x, b.y);
+            }
+            re += r.value();
+            im += m.value();
+        } else if (!pairs && join_chosen(sc)) {
             // the pair join: the blocks' partials in block order, only
             // those its hit map flags (the others were never written)
             uint32_t w[kJoinMaxBlocks];
@@ -2140,6 +2159,7 @@ __global__ void batch_reset_kernel(const JobDesc *__restrict__ jobs, int n_jobs,
 
 __global__ void batch_clear_kernel(const JobDesc *__restrict__ jobs) {
     const JobDesc &J = jobs[blockIdx.y];
+    if (J.sc.pairs) return;  // (a launch of its own prepares the job)
     const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
     const int words = (J.kind & 1) + 1;
     if (s < J.capacity) {
@@ -2160,7 +2180,7 @@ __global__ void batch_clear_kernel(const JobDesc *__restrict__ jobs) {
 __global__ void batch_build_kernel(const JobDesc *__restrict__ jobs) {
     const JobDesc &J = jobs[blockIdx.y];
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= J.n) return;
+    if (i >= J.n || J.sc.pairs) return;
     if ((J.kind & 1) == 0)
         hash_build_one<1>(J.tab, J.sc, J.samples, J.weights, i);
     else
@@ -2364,7 +2384,13 @@ hipError_t launch_batch(const JobDesc *d_jobs, int n_jobs, const WorkItem *d_ite
     // kernels below skip a job the join takes)
     for (int k = 0; h_jobs && k < n_jobs; ++k) {
         const JobDesc &J = h_jobs[k];
-        if (!J.sc.jctl || J.n == 0) continue;
+        if (J.n == 0) continue;
+        if (J.sc.pairs) {
+            const hipError_t e = launch_pairs_prep(J.tab, J.sc, J.samples, J.weights, J.log_amp,
+                                                   J.phase, J.n, st);
+            if (e != hipSuccess) return e;
+        }
+        if (!J.sc.jctl) continue;
         const hipError_t e = launch_join_prep(J.tab, J.sc, J.samples, J.weights, J.n,
                                               J.tab.n_groups - (J.tab.has_diagonal ? 1 : 0),
                                               false, st);
@@ -2397,8 +2423,14 @@ hipError_t launch_batch(const JobDesc *d_jobs, int n_jobs, const WorkItem *d_ite
     }
     for (int k = 0; h_jobs && k < n_jobs; ++k) {
         const JobDesc &J = h_jobs[k];
-        if (!J.sc.jctl || J.n == 0) continue;
+        if (J.n == 0) continue;
         const int pr = (J.kind & kJobIntegrals) ? NQS_FP64 : precision;
+        if (J.sc.pairs) {
+            const hipError_t e = launch_pairs(J.tab, J.sc, J.log_amp, J.phase, J.n, pr, nullptr,
+                                              nullptr, 0, st);
+            if (e != hipSuccess) return e;
+        }
+        if (!J.sc.jctl) continue;
         const hipError_t e = launch_join_pairs(J.tab, J.sc, J.samples, J.weights, 0, J.log_amp,
                                                J.phase, J.n, pr, nullptr, nullptr, 0, st);
         if (e != hipSuccess) return e;
@@ -2548,6 +2580,30 @@ int device_cus() {
 }
 }  // namespace
 
+namespace {
+// Largest batch that goes to the comparison of all pairs without grouping
+// its samples first.
+constexpr int64_t kPairsDirect = 8192;
+
+// Whether comparing all pairs of n samples takes less time than the
+// strategy beside the pair join: the enumeration of a half-filled sector, or
+// streaming.  Picoseconds on MI355X: a pair 0.09 (11.5 us for 8,192 samples
+// at 100 qubits, 5 of them the launch), a connected pair 100 against 300 of
+// the enumeration (37,843 gathered samples at 40 qubits with 17 M hits: 1.85
+// ms against 3.31), a lookup of the enumeration 0.47 (70.9 ms for 1.5 10^11)
+// and 6 10^7 for the hash it needs, a streamed pair 1.2 (20,000 groups past
+// 10,007 samples: 240 us); a near pair that the group index decides 2.
+bool pairs_cheaper(const DevTable &tab, int64_t n) {
+    // (the pair kernel packs a sample's index in 27 bits)
+    if (n > kJoinMaxSamples) return false;
+    const double dn = static_cast<double>(n);
+    const double cost = dn * dn * (0.09 + 2.0 * tab.near_share);
+    if (!tab.enum_ok) return cost < 1.2 * dn * static_cast<double>(tab.n_groups) + 4.0e7;
+    const double hits = dn * tab.half_flips * std::fmin(1.0, dn / tab.half_states);
+    return cost + 100.0 * hits < 0.47 * dn * tab.half_flips + 300.0 * hits + 6.0e7;
+}
+}  // namespace
+
 EvalLaunch plan_eval(const DevTable &tab, int64_t n, bool dump, const Tuning *tune) {
     EvalLaunch L;
     L.n = n;
@@ -2604,12 +2660,35 @@ EvalLaunch plan_eval(const DevTable &tab, int64_t n, bool dump, const Tuning *tu
         L.join_force = want == kStrategyJoin ? 1 : 0;
         L.join_log2m = join_log2m_for(n);
     }
+    L.join_scratch = L.join;
+    L.pairs = 0;
+    L.pairs_split = 1;
+    if (want == kStrategyAuto && pairs_cheaper(tab, n)) {
+        L.pairs = L.join && n > kPairsDirect ? 2 : 1;
+        if (L.pairs == 1) L.join = 0;
+        // two shares of the columns where one leaves compute units idle (a
+        // share's partial takes the room of two)
+        const int64_t room = L.join_scratch ? tab.join_blocks : 0;
+        if ((n + 31) / 32 < 2 * device_cus() && (L.n_chunks > room ? L.n_chunks : room) >= 4)
+            L.pairs_split = 2;
+    }
     return L;
 }
 
 hipError_t launch_hash(const DevTable &tab, const DevScratch &sc, uint32_t capacity,
-                       const uint64_t *samples, const int64_t *weights, int64_t n,
-                       hipStream_t st, hipEvent_t after_grouping, bool join_only) {
+                       const uint64_t *samples, const int64_t *weights, const double *log_amp,
+                       const double *phase, int64_t n, hipStream_t st, hipEvent_t after_grouping,
+                       bool join_only) {
+    if (sc.pairs) {
+        // all pairs are compared (unless the join's decision is to run): no
+        // sample hash
+        hipError_t e = launch_pairs_prep(tab, sc, samples, weights, log_amp, phase, n, st);
+        if (e == hipSuccess && sc.jctl)
+            e = launch_join_prep(tab, sc, samples, weights, n,
+                                 tab.n_groups - (tab.has_diagonal ? 1 : 0), false, st);
+        if (e == hipSuccess && after_grouping) e = hipEventRecord(after_grouping, st);
+        return e;
+    }
     const int words = tab.n_qubits <= 63 ? 1 : 2;
     // with the pair join launched, its histogram kernel frees the hash slots
     // and clears the bitmaps in blocks of its own (the grouping does not use
@@ -2729,15 +2808,24 @@ hipError_t launch_eloc(const DevTable &tab, const DevScratch &sc, const EvalLaun
         // the hash build rides in the same launch (launch_hash left it out);
         // a join-only launch has none (its hash is not cleared, nothing would
         // read it, and the grouping made the sample checks)
-        e = launch_join_pairs(tab, sc, samples, weights, L.join_only ? 0 : 1, log_amp, phase, n,
-                              precision, hit_idx, sign_bits, sign_words, st);
+        e = launch_join_pairs(tab, sc, samples, weights, L.join_only || sc.pairs ? 0 : 1, log_amp,
+                              phase, n, precision, hit_idx, sign_bits, sign_words, st);
         if (e != hipSuccess) return e;
     }
     if (ev.after_pairs) {
         e = hipEventRecord(ev.after_pairs, st);
         if (e != hipSuccess) return e;
     }
-    if (en && !L.join_only) {
+    if (sc.pairs) {
+        if (hit_idx && !sc.jctl) {
+            const int64_t cnt = n * tab.n_groups;
+            hipLaunchKernelGGL(fill_i32_kernel, dim3(static_cast<unsigned>((cnt + 255) / 256)),
+                               dim3(256), 0, st, hit_idx, cnt, -1);
+        }
+        e = launch_pairs(tab, sc, log_amp, phase, n, precision, hit_idx, sign_bits, sign_words, st);
+        if (e != hipSuccess) return e;
+    }
+    if (en && !L.join_only && !sc.pairs) {
         // a dump marks every pair first; the enumeration writes only its hits
         // (done above when a join was launched too)
         if (hit_idx && !sc.jctl) {
@@ -2766,7 +2854,7 @@ hipError_t launch_eloc(const DevTable &tab, const DevScratch &sc, const EvalLaun
 #undef NQS_ENUM
         if (e != hipSuccess) return e;
     }
-    if (L.chunk_len > 0 && !L.join_only) {
+    if (L.chunk_len > 0 && !L.join_only && !sc.pairs) {
 #define NQS_LOOKUP(Wd, S, SE, D, Pr)                                                       \
     e = launch_lookup<Wd, S, SE, D, Pr, false>(tab, sc, L, samples, log_amp, phase, hit_idx,  \
                                                sign_bits, sign_words, fb, st)

@@ -1,0 +1,436 @@
+// All pairs of samples on the matrix cores: the local energy summed over the
+// pairs of S directly (Eq. 5 with the kets taken from S, the loop structure
+// of Alg. 3), for batches small enough, or gathered enough, that comparing
+// every pair costs less than grouping the samples or enumerating their
+// flips.
+//
+// Every group of the table flips at most max_flip qubits, so a connected
+// pair is within that Hamming distance.  With the bits of a sample as +-1,
+// x . y = n_qubits - 2 distance(x, y): a tile of 32 x 32 pairs is one FP4
+// matrix product per 64 qubits (products of +-1 summed in FP32, exact), the
+// threshold sits in its C operand, and a pair is near where the result is
+// positive.  Near pairs (the group index decides whether X = x ^ y is a flip
+// of the table) are queued per wave and evaluated 64 at a time, the few
+// groups with many terms (single excitations) in a queue of their own, so
+// that a wave's lanes run alike.
+//
+// Determinism: each sample's contributions are added as double-doubles (one
+// rounding of a sum whose error is below 2^-100 of its largest partial), so
+// the bits of the result do not depend on the order of the additions.
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "../../include/nqs.h"
+#include "nqs_dev_common.hpp"
+#include "nqs_device.hpp"
+
+namespace nqs {
+
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+constexpr int kPairsThreads = 512;
+constexpr int kPairsWaves = kPairsThreads / 64;
+constexpr int kPairsQueue = 128;  // entries per queue and wave (64 are taken at a time)
+// Groups of more terms than this go through the queue of long groups: the
+// double excitations of a molecule have 4 or 6 terms, its single
+// excitations 2 n_qubits - 2.
+constexpr uint32_t kShortTerms = 12;
+
+struct alignas(16) PairRec {
+    uint64_t w0, w1;
+    double la, ph;
+};
+
+// Bits of v as 32 nibbles of FP4 +1 (0x2) or -1 (0xA), 0 where valid is 0.
+__device__ __forceinline__ v4i fp4_signs(uint32_t v, uint32_t valid) {
+    v4i r;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        uint32_t b = (~v >> (8 * k)) & 0xFFu, m = (valid >> (8 * k)) & 0xFFu;
+        // one bit per nibble
+        b = (b | (b << 12)) & 0x000F000Fu;
+        b = (b | (b << 6)) & 0x03030303u;
+        b = (b | (b << 3)) & 0x11111111u;
+        m = (m | (m << 12)) & 0x000F000Fu;
+        m = (m | (m << 6)) & 0x03030303u;
+        m = (m | (m << 3)) & 0x11111111u;
+        r[k] = static_cast<int>(((b << 3) & (m << 3)) | (m << 1));
+    }
+    return r;
+}
+
+// Clears the counters and control words of the launch, makes the sample
+// checks of the hash build, and lays out the samples for the pair kernel:
+// the FP4 operand of each 32-sample tile (lane L of k-block kb: sample
+// L % 32, qubits 64 kb + 32 (L / 32) .. + 31) and one 32-byte record per
+// sample.
+template <int W>
+__global__ __launch_bounds__(256) void pairs_prep_kernel(
+    DevTable tab, DevScratch sc, const uint64_t *__restrict__ samples,
+    const int64_t *__restrict__ weights, const double *__restrict__ log_amp,
+    const double *__restrict__ phase, int64_t n, uint32_t jparts, uint32_t jhit_words) {
+    const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s < static_cast<uint32_t>(kCounters * kCounterSlots)) sc.counters[s] = 0;
+    if (s == 0) *sc.mixed = 0;
+    if (sc.jctl && s < static_cast<uint32_t>(kJoinCtl)) sc.jctl[s] = 0;
+    if (s < jparts) sc.jcnt[s] = 0u;
+    if (s < jhit_words) sc.jhit[s] = 0u;
+    const int64_t tiles = (n + 31) / 32;
+    const int nq = tab.n_qubits;
+    if (s < tiles * W * 64) {
+        const int lane = static_cast<int>(s & 63u);
+        const int64_t tk = s >> 6;
+        const int kb = W == 2 ? static_cast<int>(tk & 1) : 0;
+        const int64_t i = (W == 2 ? tk >> 1 : tk) * 32 + (lane & 31);
+        v4i r = {0, 0, 0, 0};
+        if (i < n) {
+            const int q0 = 64 * kb + 32 * (lane >> 5);
+            const int left = nq - q0;
+            const uint32_t valid =
+                left >= 32 ? 0xFFFFFFFFu : (left <= 0 ? 0u : (1u << left) - 1u);
+            r = fp4_signs(static_cast<uint32_t>(samples[2 * i + kb] >> (32 * (lane >> 5))),
+                          valid);
+        }
+        reinterpret_cast<v4i *>(sc.pops)[s] = r;
+    }
+    if (s < n) {
+        const int64_t i = s;
+        const uint64_t w0 = samples[2 * i], w1 = samples[2 * i + 1];
+        const bool bad = nq >= 64 ? ((w1 >> (nq - 64)) != 0) : ((w0 >> nq) != 0 || w1 != 0);
+        if (bad || (weights && weights[i] < 0)) latch(sc.err, NQS_E_RANGE);
+        PairRec r{w0, w1, log_amp[i], phase[i]};
+        reinterpret_cast<PairRec *>(sc.prec)[i] = r;
+    }
+}
+
+template <int W>
+__device__ __forceinline__ Key<W> rec_key(const PairRec &r) {
+    Key<W> k;
+    k.w[0] = r.w0;
+    if constexpr (W == 2) k.w[W - 1] = r.w1;
+    return k;
+}
+
+// Shared state of one wave.
+struct PairsWave {
+    uint32_t q[kPairsQueue];       // near pairs: x of the tile | y << 5
+    uint2 lq[kPairsQueue];         // pairs whose group is long: the same, group
+    double con[2][64];             // contributions of a batch (re, im)
+    unsigned long long own[32];    // which of them belong to each x
+};
+
+// One block per 32 samples x (blockIdx.x) and share of the samples y
+// (blockIdx.y); its waves take the tiles of y in turn.
+//
+// Bound: per 32 x 32 pairs one (W = 1) or two FP4 MFMAs of 32 cycles and
+// about ten VALU instructions where no pair is near; per near pair the
+// gathers of its record, group and terms, and the FP64 amplitude ratio.
+template <int W, bool DUMP, int P, bool SCV>
+__global__ __launch_bounds__(kPairsThreads) void pairs_kernel(
+    DevTable tab, DevScratch sc, int64_t n, const double *__restrict__ log_amp,
+    const double *__restrict__ phase, int32_t *__restrict__ hit_idx,
+    uint32_t *__restrict__ sign_bits, int64_t sign_words) {
+    if (!pairs_chosen(sc)) return;
+    __shared__ PairRec xs[32];
+    __shared__ uint32_t hr[128];
+    __shared__ PairsWave waves[kPairsWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t x0 = static_cast<int64_t>(blockIdx.x) * 32;
+    const PairRec *__restrict__ rec = reinterpret_cast<const PairRec *>(sc.prec);
+    if (threadIdx.x < 32) {
+        const int64_t i = x0 + threadIdx.x;
+        xs[threadIdx.x] = i < n ? rec[i] : PairRec{0, 0, 0.0, 0.0};
+    }
+    if (threadIdx.x < 128) hr[threadIdx.x] = tab.hr[threadIdx.x];
+    __syncthreads();
+    PairsWave &me = waves[wave];
+    const int comp = lane >> 5, xl = lane & 31;  // this lane sums component comp of x xl
+    Acc2 acc;
+    unsigned long long n_probe = 0, n_hit = 0, n_term = 0;
+
+    // the contributions con[.][0..63] of the lanes in valid (x: the lane's
+    // sample of the tile) into the owners' sums
+    auto deposit = [&](bool valid, uint32_t x, double re, double im) {
+        me.con[0][lane] = re;
+        me.con[1][lane] = im;
+        if (lane < 32) me.own[lane] = 0ull;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        if (valid) atomicOr(&me.own[x], 1ull << lane);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        unsigned long long mine = me.own[xl];
+        while (mine) {
+            const int k = __builtin_ctzll(mine);
+            mine &= mine - 1;
+            acc.add(me.con[comp][k]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    };
+    // <x|H|y> psi(y) / psi(x) of a pair whose group is g
+    auto evaluate = [&](const PairRec &x, const PairRec &y, int64_t i, int64_t g, double &re,
+                        double &im) {
+        const Key<W> xk = rec_key<W>(x);
+        if constexpr (P == NQS_FP64) {
+            double h;
+            if constexpr (SCV) {
+                h = sc_element<W>(tab, xk, rec_key<W>(y));
+            } else {
+                uint32_t *row = (DUMP && sign_bits) ? sign_bits + i * sign_words : nullptr;
+                h = group_sum<W, DUMP>(tab, g, xk, row, &n_term);
+            }
+            const double2 rat = amp_ratio_f64(y.la - x.la, y.ph - x.ph);
+            re = h * rat.x;
+            im = h * rat.y;
+        } else {
+            const AccF32 h = group_sum_f32<W>(tab, g, xk, &n_term);
+            float rr, ri;
+            ratio_f32(y.la - x.la, y.ph - x.ph, rr, ri);
+            const float pre = h.s * rr, pim = h.s * ri;
+            re = static_cast<double>(pre) + static_cast<double>(fmaf(h.s, rr, -pre) + h.c * rr);
+            im = static_cast<double>(pim) + static_cast<double>(fmaf(h.s, ri, -pim) + h.c * ri);
+        }
+    };
+    uint32_t qn = 0, ln = 0;  // queue lengths (the same in every lane)
+    auto flush_long = [&](uint32_t m) {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        const bool on = lane < static_cast<int>(m);
+        uint32_t x = 0;
+        double re = 0.0, im = 0.0;
+        if (on) {
+            const uint2 e = me.lq[lane];
+            x = e.x & 31u;
+            evaluate(xs[x], rec[e.x >> 5], x0 + x, e.y, re, im);
+        }
+        deposit(on, x, re, im);
+    };
+    auto flush = [&](uint32_t m) {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        bool now = false, later = false;
+        uint32_t e = 0, x = 0;
+        int64_t g = -1;
+        double re = 0.0, im = 0.0;
+        if (lane < static_cast<int>(m)) {
+            e = me.q[lane];
+            x = e & 31u;
+            const int64_t i = x0 + x, j = e >> 5;
+            if (i != j) {
+                const PairRec y = rec[j];
+                const Key<W> xk = rec_key<W>(xs[x]), yk = rec_key<W>(y);
+                Key<W> d;
+                uint64_t any = 0;
+                int pop = 0;
+#pragma unroll
+                for (int w = 0; w < W; ++w) {
+                    d.w[w] = xk.w[w] ^ yk.w[w];
+                    any |= d.w[w];
+                    pop += __popcll(d.w[w]);
+                }
+                if (any == 0ull) {
+                    latch(sc.err, NQS_E_DUPLICATE);
+                } else {
+                    ++n_probe;
+                    g = group_find<W>(tab, linear_hash<W>(d, hr), d);
+                    if constexpr (DUMP) {
+                        if (hit_idx && g >= 0)
+                            hit_idx[i * tab.n_groups + g] = static_cast<int32_t>(j);
+                    }
+                    if (g >= 0) {
+                        ++n_hit;
+                        later = SCV ? pop == 2 : tab.goff[g + 1] - tab.goff[g] > kShortTerms;
+                        now = !later;
+                        if (now) evaluate(xs[x], y, i, g, re, im);
+                    }
+                }
+            }
+        }
+        const uint64_t lm = __ballot(later);
+        if (later) me.lq[ln + lanes_below(lm)] = make_uint2(e, static_cast<uint32_t>(g));
+        ln += static_cast<uint32_t>(__popcll(lm));
+        deposit(now, x, re, im);
+        if (ln >= 64) {
+            flush_long(64);
+            ln -= 64;
+            if (lane < static_cast<int>(ln)) me.lq[lane] = me.lq[64 + lane];
+        }
+    };
+
+    // the x operand, resident; the C operand: near pairs come out positive
+    const v4i *__restrict__ ops = reinterpret_cast<const v4i *>(sc.pops);
+    v8i xo[W];
+#pragma unroll
+    for (int kb = 0; kb < W; ++kb) {
+        const v4i o = ops[(static_cast<int64_t>(blockIdx.x) * W + kb) * 64 + lane];
+        xo[kb] = v8i{o[0], o[1], o[2], o[3], 0, 0, 0, 0};
+    }
+    const float thr = 0.5f - static_cast<float>(tab.n_qubits - 2 * tab.max_flip);
+    v16f cthr;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) cthr[r] = thr;
+    const bool x_in = x0 + xl < n;
+    const int tiles = static_cast<int>((n + 31) / 32);
+    const int step = kPairsWaves * static_cast<int>(gridDim.y);
+    int t = wave + kPairsWaves * static_cast<int>(blockIdx.y);
+    v4i next[W];
+#pragma unroll
+    for (int kb = 0; kb < W; ++kb) next[kb] = v4i{0, 0, 0, 0};
+    if (t < tiles) {
+#pragma unroll
+        for (int kb = 0; kb < W; ++kb) next[kb] = ops[(static_cast<int64_t>(t) * W + kb) * 64 + lane];
+    }
+    for (; t < tiles; t += step) {
+        v16f c = cthr;
+#pragma unroll
+        for (int kb = 0; kb < W; ++kb) {
+            const v8i a = v8i{next[kb][0], next[kb][1], next[kb][2], next[kb][3], 0, 0, 0, 0};
+            c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, xo[kb], c, 4, 4, 0, 0, 0, 0);
+        }
+        if (t + step < tiles) {
+#pragma unroll
+            for (int kb = 0; kb < W; ++kb)
+                next[kb] = ops[(static_cast<int64_t>(t + step) * W + kb) * 64 + lane];
+        }
+        float mx = c[0];
+#pragma unroll
+        for (int r = 1; r < 15; r += 2) mx = fmaxf(fmaxf(mx, c[r]), c[r + 1]);
+        mx = fmaxf(mx, c[15]);
+        if (__ballot(mx > 0.0f) == 0ull) continue;
+        // bit 15 - r: value r is positive (lane's x = lane % 32, its y are
+        // rows 8 (r / 4) + 4 (lane / 32) + r % 4 of the tile)
+        uint32_t neg = 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            neg = (neg << 1) | (__float_as_uint(c[r]) >> 31);
+        uint32_t near = ~neg & 0xFFFFu;
+        if (!x_in) near = 0;
+        const int64_t y0 = static_cast<int64_t>(t) * 32;
+        if (y0 + 32 > n) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (y0 + 8 * (r >> 2) + 4 * comp + (r & 3) >= n) near &= ~(1u << (15 - r));
+        }
+        for (;;) {
+            const uint64_t any = __ballot(near != 0u);
+            if (!any) break;
+            if (near) {
+                const int r = __builtin_clz(near) - 16;
+                near &= ~(0x8000u >> r);
+                const uint32_t y = static_cast<uint32_t>(y0) + 8 * (r >> 2) + 4 * comp + (r & 3);
+                me.q[qn + lanes_below(any)] = static_cast<uint32_t>(xl) | (y << 5);
+            }
+            qn += static_cast<uint32_t>(__popcll(any));
+            if (qn >= 64) {
+                flush(64);
+                qn -= 64;
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                if (lane < static_cast<int>(qn)) me.q[lane] = me.q[64 + lane];
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            }
+        }
+    }
+    if (qn) flush(qn);
+    if (ln) flush_long(ln);
+    // the waves' sums in wave order (through the contribution arrays)
+    me.con[0][lane] = acc.hi;
+    me.con[1][lane] = acc.lo;
+    __syncthreads();
+    if (wave == 0) {
+        Acc2 s;
+        for (int w = 0; w < kPairsWaves; ++w) s.add(waves[w].con[0][lane], waves[w].con[1][lane]);
+        const int64_t i = x0 + xl;
+        if (i < n) {
+            if (gridDim.y == 1) {
+                sc.part[2 * i + comp] = s.value();
+            } else {
+                double *p = sc.part + 4 * (static_cast<int64_t>(blockIdx.y) * n + i) + 2 * comp;
+                p[0] = s.hi;
+                p[1] = s.lo;
+            }
+        }
+    }
+    // counters, one set of atomics per wave
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        n_probe += __shfl_xor(n_probe, off);
+        n_hit += __shfl_xor(n_hit, off);
+        n_term += __shfl_xor(n_term, off);
+    }
+    if (lane == 0) {
+        count_add(sc.counters, 1, n_probe);
+        count_add(sc.counters, 2, n_hit);
+        count_add(sc.counters, 3, n_term);
+    }
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+        count_add(sc.counters, 4,
+                  static_cast<unsigned long long>(n) * static_cast<unsigned long long>(n - 1));
+}
+
+template <int W>
+hipError_t launch_prep_w(const DevTable &tab, const DevScratch &sc, const uint64_t *samples,
+                         const int64_t *weights, const double *log_amp, const double *phase,
+                         int64_t n, hipStream_t st) {
+    const uint32_t jparts = sc.jctl ? static_cast<uint32_t>(sc.join_parts) : 0u;
+    const uint32_t jhw =
+        sc.jctl ? static_cast<uint32_t>((tab.join_blocks * n + 31) / 32) : 0u;
+    int64_t span = (n + 31) / 32 * W * 64;
+    const int64_t least[] = {kCounters * kCounterSlots, kJoinCtl, jparts, jhw, n};
+    for (int64_t v : least) span = v > span ? v : span;
+    hipLaunchKernelGGL(pairs_prep_kernel<W>, dim3(static_cast<unsigned>((span + 255) / 256)),
+                       dim3(256), 0, st, tab, sc, samples, weights, log_amp, phase, n, jparts, jhw);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+size_t pairs_scratch_bytes(const DevTable &tab, int64_t n) {
+    const int words = tab.n_qubits <= 63 ? 1 : 2;
+    return static_cast<size_t>((n + 31) / 32) * 32 * 32 * words + sizeof(PairRec) * n;
+}
+
+void pairs_scratch_layout(const DevTable &tab, int64_t n, char *base, DevScratch *sc) {
+    const int words = tab.n_qubits <= 63 ? 1 : 2;
+    sc->pops = base;
+    sc->prec = base + static_cast<size_t>((n + 31) / 32) * 32 * 32 * words;
+}
+
+hipError_t launch_pairs_prep(const DevTable &tab, const DevScratch &sc, const uint64_t *samples,
+                             const int64_t *weights, const double *log_amp, const double *phase,
+                             int64_t n, hipStream_t st) {
+    return tab.n_qubits <= 63
+               ? launch_prep_w<1>(tab, sc, samples, weights, log_amp, phase, n, st)
+               : launch_prep_w<2>(tab, sc, samples, weights, log_amp, phase, n, st);
+}
+
+hipError_t launch_pairs(const DevTable &tab, const DevScratch &sc, const double *log_amp,
+                        const double *phase, int64_t n, int precision, int32_t *hit_idx,
+                        uint32_t *sign_bits, int64_t sign_words, hipStream_t st) {
+    const bool dump = hit_idx || sign_bits;
+    const bool f32 = precision == NQS_FP32_KAHAN && !dump && !tab.sc;
+    const dim3 grid(static_cast<unsigned>((n + 31) / 32), static_cast<unsigned>(sc.pairs_split));
+#define NQS_AP(Wd, D, Pr, SCI)                                                                  \
+    hipLaunchKernelGGL((pairs_kernel<Wd, D, Pr, SCI>), grid, dim3(kPairsThreads), 0, st, tab, sc, \
+                       n, log_amp, phase, hit_idx, sign_bits, sign_words)
+    const bool w1 = tab.n_qubits <= 63;
+    if (tab.sc) {
+        if (w1) {
+            if (dump) NQS_AP(1, true, NQS_FP64, true); else NQS_AP(1, false, NQS_FP64, true);
+        } else {
+            if (dump) NQS_AP(2, true, NQS_FP64, true); else NQS_AP(2, false, NQS_FP64, true);
+        }
+    } else if (w1) {
+        if (dump) NQS_AP(1, true, NQS_FP64, false);
+        else if (f32) NQS_AP(1, false, NQS_FP32_KAHAN, false);
+        else NQS_AP(1, false, NQS_FP64, false);
+    } else {
+        if (dump) NQS_AP(2, true, NQS_FP64, false);
+        else if (f32) NQS_AP(2, false, NQS_FP32_KAHAN, false);
+        else NQS_AP(2, false, NQS_FP64, false);
+    }
+#undef NQS_AP
+    return hipGetLastError();
+}
+
+}  // namespace nqs
