@@ -640,12 +640,22 @@ int create_handle(nqs_ham *out, const nqs::HostTable &T, const std::vector<doubl
     if (T.n_groups >= kMaxGroups) return fail(NQS_E_ARG, "more than 2^26 X groups");
     const int64_t G = T.n_groups, Tn = T.n_terms;
     // one allocation holding every table array, each 256-byte aligned
-    std::vector<float> tc32(2 * static_cast<size_t>(Tn));
-    for (int64_t t = 0; t < Tn; ++t) {
-        const float hi = static_cast<float>(T.tc[t]);
-        tc32[2 * t] = hi;
-        tc32[2 * t + 1] = static_cast<float>(T.tc[t] - static_cast<double>(hi));
+    // the group records and the group index; the integral form keeps the flip
+    // masks and group numbers alone
+    nqs::GroupRecords R;
+    std::vector<uint64_t> index;
+    if (!h1) {
+        nqs::build_group_records(T, &R);
+        index.resize(T.gh.size());
+        for (size_t s = 0; s < index.size(); ++s) {
+            const uint32_t g = T.gh[s];
+            index[s] = ~0ull;
+            if (g == 0xFFFFFFFFu) continue;
+            const uint64_t terms = std::min<int64_t>(T.goff[g + 1] - T.goff[g], 255);
+            index[s] = g | (terms << 32) | (static_cast<uint64_t>(T.ghm[2 * g] & 0xFFFFFFu) << 40);
+        }
     }
+    const std::vector<uint64_t> &gx = h1 ? T.gx : R.rec;
     std::vector<float> diag32(2 * T.diag.size());
     for (size_t k = 0; k < T.diag.size(); ++k) {
         const float hi = static_cast<float>(T.diag[k]);
@@ -666,22 +676,24 @@ int create_handle(nqs_ham *out, const nqs::HostTable &T, const std::vector<doubl
         size_t off;
     };
     Piece pieces[] = {
-        {T.gx.data(), sizeof(uint64_t) * T.gx.size(), 0},
+        {gx.data(), sizeof(uint64_t) * gx.size(), 0},
         {T.gsec.data(), sizeof(uint64_t) * T.gsec.size(), 0},
         {T.ghm.data(), sizeof(uint32_t) * T.ghm.size(), 0},
         {goff32.data(), sizeof(uint32_t) * goff32.size(), 0},
-        {T.tz.data(), sizeof(uint64_t) * T.tz.size(), 0},
+        {R.z.data(), sizeof(uint64_t) * R.z.size(), 0},
         {T.tc.data(), sizeof(double) * T.tc.size(), 0},
-        {tc32.data(), sizeof(float) * tc32.size(), 0},
+        {R.codes.data(), R.codes.size(), 0},
         {lh.r, sizeof(lh.r), 0},
         {h1 ? h1->data() : nullptr, h1 ? sizeof(double) * h1->size() : 0, 0},
         {eri ? eri->data() : nullptr, eri ? sizeof(double) * eri->size() : 0, 0},
         {T.spin_q, sizeof(T.spin_q), 0},
-        {T.gh.data(), sizeof(uint32_t) * T.gh.size(), 0},
+        {h1 ? static_cast<const void *>(T.gh.data()) : index.data(),
+         h1 ? sizeof(uint32_t) * T.gh.size() : sizeof(uint64_t) * index.size(), 0},
         {T.qcls, sizeof(T.qcls), 0},
         {T.diag.data(), sizeof(double) * T.diag.size(), 0},
         {diag32.data(), sizeof(float) * diag32.size(), 0},
         {diag_q8.data(), diag_q8.size(), 0},
+        {R.rows.data(), sizeof(double) * R.rows.size(), 0},
     };
     size_t total = 0;
     for (Piece &p : pieces) {
@@ -727,12 +739,14 @@ int create_handle(nqs_ham *out, const nqs::HostTable &T, const std::vector<doubl
     h->words = T.words;
     nqs::DevTable &d = h->dt;
     d.gx = reinterpret_cast<const uint64_t *>(base + pieces[0].off);
+    d.gx_stride = h1 ? 2 : nqs::kGroupWords;
     d.gsec = reinterpret_cast<const uint64_t *>(base + pieces[1].off);
     d.ghm = reinterpret_cast<const uint32_t *>(base + pieces[2].off);
     d.goff = reinterpret_cast<const uint32_t *>(base + pieces[3].off);
     d.tz = reinterpret_cast<const uint64_t *>(base + pieces[4].off);
     d.tc = reinterpret_cast<const double *>(base + pieces[5].off);
-    d.tc32 = reinterpret_cast<const float *>(base + pieces[6].off);
+    d.tcode = reinterpret_cast<const uint8_t *>(base + pieces[6].off);
+    d.occ = reinterpret_cast<const double *>(base + pieces[16].off);
     d.hr = reinterpret_cast<const uint32_t *>(base + pieces[7].off);
     d.sc_h1 = h1 ? reinterpret_cast<const double *>(base + pieces[8].off) : nullptr;
     d.sc_eri = eri ? reinterpret_cast<const double *>(base + pieces[9].off) : nullptr;
@@ -752,7 +766,7 @@ int create_handle(nqs_ham *out, const nqs::HostTable &T, const std::vector<doubl
     d.k_alpha = T.k_alpha;
     d.k_beta = T.k_beta;
     d.spin_q = reinterpret_cast<const uint8_t *>(base + pieces[10].off);
-    d.gh = reinterpret_cast<const uint32_t *>(base + pieces[11].off);
+    d.gh = base + pieces[11].off;
     d.gh_shift = T.gh_shift;
     d.qcls = reinterpret_cast<const uint8_t *>(base + pieces[12].off);
     d.max_flip = T.max_flip;

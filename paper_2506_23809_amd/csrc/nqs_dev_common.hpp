@@ -183,23 +183,132 @@ __device__ __forceinline__ uint32_t filter_test(uint32_t fw, uint32_t h) {
     return (fw >> ((h >> 17) & 31)) & (fw >> ((h >> 24) & 31)) & 1u;
 }
 
+// Word q of group g's flip mask.
+template <int W>
+__device__ __forceinline__ uint64_t group_x(const DevTable &tab, int64_t g, int q) {
+    const uint64_t v = tab.gx[static_cast<size_t>(tab.gx_stride) * g + q];
+    return q == W - 1 ? v & ~kGroupGeneral : v;
+}
+
+// The bits of x at the flips X (at most four, lowest first), and their number.
+template <int W>
+__device__ __forceinline__ uint32_t flip_pattern(const Key<W> &X, const Key<W> &x, int &m) {
+    uint64_t lo = X.w[0], hi = W == 2 ? X.w[W - 1] : 0ull;
+    uint32_t pat = 0;
+    m = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if constexpr (W == 1) {
+            const uint64_t b = lo & (0ull - lo);
+            lo ^= b;
+            m += b != 0ull;
+            pat |= (x.w[0] & b) ? 1u << k : 0u;
+        } else {
+            const bool low = lo != 0ull;
+            const uint64_t v = low ? lo : hi, b = v & (0ull - v);
+            const uint64_t c = v ^ b;
+            lo = low ? c : lo;
+            hi = low ? hi : c;
+            m += b != 0ull;
+            pat |= ((low ? x.w[0] : x.w[W - 1]) & b) ? 1u << k : 0u;
+        }
+    }
+    return pat;
+}
+
+// Sum of one group's terms for bra x, sum_t c~_t (-1)^{popc(Z_t & x)}: from
+// the group's record where it is tabulated, from its occupation row where it
+// has one, else term by term.  cnt: the group's terms if known (0 or 255:
+// not).  One record of 64 bytes a hit instead of two arrays of 4 to 6 terms,
+// or of 78 (198 at 100 qubits) for a single excitation.
 template <int W, bool DUMP>
 __device__ __forceinline__ double group_sum(const DevTable &tab, int64_t g, const Key<W> &x,
                                             uint32_t *__restrict__ sign_row,
-                                            unsigned long long *terms) {
-    const uint32_t t0 = tab.goff[g], t1 = tab.goff[g + 1];
-    double s = 0.0;
-    for (uint32_t t = t0; t < t1; ++t) {
-        int par = 0;
+                                            unsigned long long *terms, uint32_t cnt = 0) {
+    if (cnt == 0u || cnt == 255u) cnt = tab.goff[g + 1] - tab.goff[g];
+    *terms += cnt;
+    const uint64_t *rec = tab.gx + static_cast<size_t>(kGroupWords) * g;
+    const uint64_t *value = rec + 2 * W;
+    Key<W> X;
+    int par = 0;
 #pragma unroll
-        for (int q = 0; q < W; ++q) par += __popcll(tab.tz[2 * static_cast<size_t>(t) + q] & x.w[q]);
-        const double c = tab.tc[t];
-        s += (par & 1) ? -c : c;
+    for (int q = 0; q < W; ++q) {
+        X.w[q] = rec[q];
+        par += __popcll(rec[W + q] & x.w[q]);
+    }
+    const bool general = (X.w[W - 1] & kGroupGeneral) != 0ull;
+    X.w[W - 1] &= ~kGroupGeneral;
+    double s = 0.0;
+    if (!general) {
+        int m;
+        const uint32_t pat = flip_pattern<W>(X, x, m);
+        // relative to the first flip
+        const uint32_t rel = ((pat & 1u) ? ~pat : pat) & ((1u << m) - 1u);
         if constexpr (DUMP) {
-            if (sign_row && (par & 1)) atomicOr(&sign_row[t >> 5], 1u << (t & 31));
+            if (sign_row) {
+                const uint32_t t0 = tab.goff[g];
+                for (uint32_t t = t0; t < t0 + cnt; ++t)
+                    if ((par + __popc(tab.tcode[t] & pat)) & 1)
+                        atomicOr(&sign_row[t >> 5], 1u << (t & 31));
+            }
+        }
+        if (m == 4 && (__popc(rel) & 1)) {
+            // odd parity (samples of several sectors): the terms
+            const uint32_t t0 = tab.goff[g];
+            for (uint32_t t = t0; t < t0 + cnt; ++t)
+                s += (__popc(tab.tcode[t] & rel) & 1) ? -tab.tc[t] : tab.tc[t];
+        } else {
+            s = reinterpret_cast<const double *>(value)[(rel >> 1) & 3u];
+        }
+        return (par & 1) ? -s : s;
+    }
+    if (!DUMP && value[2] != 0ull) {
+        // occupied qubits four at a time (the last entry of a row is 0)
+        const int nq = tab.n_qubits;
+        uint64_t lo = x.w[0], hi = W == 2 ? x.w[W - 1] : 0ull;
+        int in = 0;  // flips of X that are occupied
+#pragma unroll
+        for (int q = 0; q < W; ++q) in += __popcll(X.w[q] & x.w[q]);
+        const double *row = tab.occ + (2 * (value[2] - 1ull) + (in & 1)) * (nq + 2);
+        s = row[0];
+        while (lo | hi) {
+            double v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                int at = nq + 1;
+                if constexpr (W == 1) {
+                    if (lo) at = 1 + __builtin_ctzll(lo);
+                    lo &= lo - 1;
+                } else {
+                    const bool low = lo != 0ull;
+                    const uint64_t b = low ? lo : hi;
+                    if (b) at = (low ? 1 : 65) + __builtin_ctzll(b);
+                    const uint64_t c = b & (b - 1);
+                    lo = low ? c : lo;
+                    hi = low ? hi : c;
+                }
+                v[k] = row[at];
+            }
+            s += v[0];
+            s += v[1];
+            s += v[2];
+            s += v[3];
+        }
+        return (par & 1) ? -s : s;
+    }
+    const uint32_t t0 = tab.goff[g];
+    const uint64_t *z = tab.tz + 2 * value[3];
+    for (uint32_t k = 0; k < cnt; ++k) {
+        int odd = 0;
+#pragma unroll
+        for (int q = 0; q < W; ++q) odd += __popcll(z[2 * static_cast<size_t>(k) + q] & x.w[q]);
+        const double c = tab.tc[t0 + k];
+        s += (odd & 1) ? -c : c;
+        if constexpr (DUMP) {
+            const uint32_t t = t0 + k;
+            if (sign_row && (odd & 1)) atomicOr(&sign_row[t >> 5], 1u << (t & 31));
         }
     }
-    *terms += t1 - t0;
     return s;
 }
 
@@ -336,11 +445,11 @@ __device__ __forceinline__ double sc_diagonal(const DevTable &tab, const Key<W> 
 
 // ---- FP32 form with compensation (precision NQS_FP32_KAHAN)
 //
-// Coefficients are stored as FP32 pairs hi + lo (lo = c - hi rounded), the
-// sign (-1)^{popc(Z & x)} is applied by flipping sign bits, the hi parts
-// are added with Knuth's error-free TwoSum and the lo parts and the TwoSum
-// errors go into a compensation term; a product H * r keeps its rounding
-// error through fma.  The per-sample value s + c is widened to FP64 only
+// A group's sum enters as an FP32 pair hi + lo (of its FP64 value); the terms
+// of a diagonal in term form likewise, with the sign (-1)^{popc(Z & x)}
+// applied by flipping sign bits.  The hi parts are added with Knuth's
+// error-free TwoSum and the lo parts and the TwoSum errors go into a
+// compensation term; a product H * r keeps its rounding error through fma.  The per-sample value s + c is widened to FP64 only
 // when it leaves the lane.
 
 __device__ __forceinline__ void two_sum(float a, float b, float &s, float &e) {
@@ -366,19 +475,14 @@ struct AccF32 {
     }
 };
 
+// The same sum for the FP32 form: the FP64 sum as an FP32 pair.
 template <int W>
 __device__ __forceinline__ AccF32 group_sum_f32(const DevTable &tab, int64_t g, const Key<W> &x,
-                                                unsigned long long *terms) {
-    const uint32_t t0 = tab.goff[g], t1 = tab.goff[g + 1];
+                                                unsigned long long *terms, uint32_t cnt = 0) {
+    const double v = group_sum<W, false>(tab, g, x, nullptr, terms, cnt);
     AccF32 a;
-    for (uint32_t t = t0; t < t1; ++t) {
-        int par = 0;
-#pragma unroll
-        for (int q = 0; q < W; ++q) par += __popcll(tab.tz[2 * static_cast<size_t>(t) + q] & x.w[q]);
-        a.add(flip_sign(tab.tc32[2 * static_cast<size_t>(t)], par),
-              flip_sign(tab.tc32[2 * static_cast<size_t>(t) + 1], par));
-    }
-    *terms += t1 - t0;
+    a.s = static_cast<float>(v);
+    a.c = static_cast<float>(v - static_cast<double>(a.s));
     return a;
 }
 
@@ -406,17 +510,31 @@ __device__ __forceinline__ void ratio_f32(double da, double dphi, float &rr, flo
 }
 
 // Index of the group with flip mask X, or -1 (the group index is keyed by
-// h(X), which the caller has: h(x') ^ h(x)).
-template <int W>
-__device__ __forceinline__ int64_t group_find(const DevTable &tab, uint32_t hX, const Key<W> &X) {
+// h(X), which the caller has: h(x') ^ h(x)); *cnt receives its terms (255:
+// or more; the integral form has none).
+template <int W, bool SCV>
+__device__ __forceinline__ int64_t group_find(const DevTable &tab, uint32_t hX, const Key<W> &X,
+                                              uint32_t *cnt) {
     const uint32_t mask = 0xFFFFFFFFu >> tab.gh_shift;
     uint32_t slot = slot_of(hX, tab.gh_shift);
     for (uint32_t probe = 0; probe <= mask; ++probe) {
-        const uint32_t g = tab.gh[slot];
-        if (g == 0xFFFFFFFFu) return -1;
-        bool eq = tab.gx[2 * static_cast<size_t>(g)] == X.w[0];
-        if constexpr (W == 2) eq = eq && tab.gx[2 * static_cast<size_t>(g) + 1] == X.w[1];
-        if (eq) return g;
+        uint32_t g;
+        bool eq = true;
+        if constexpr (SCV) {
+            g = static_cast<const uint32_t *>(tab.gh)[slot];
+            if (g == 0xFFFFFFFFu) return -1;
+        } else {
+            const uint64_t v = static_cast<const uint64_t *>(tab.gh)[slot];
+            if (v == ~0ull) return -1;
+            g = static_cast<uint32_t>(v);
+            *cnt = static_cast<uint32_t>(v >> 32) & 0xFFu;
+            eq = (v >> 40) == (hX & 0xFFFFFFu);
+        }
+        if (eq) {
+#pragma unroll
+            for (int q = 0; q < W; ++q) eq = eq && group_x<W>(tab, g, q) == X.w[q];
+            if (eq) return g;
+        }
         slot = (slot + 1) & mask;
     }
     return -1;

@@ -24,13 +24,16 @@ constexpr int kJoinMaxBlocks = 8;
 
 // Resident Pauli table (structure of arrays, all device pointers).
 struct DevTable {
-    const uint64_t *gx;    // [G][2] flip masks
+    const uint64_t *gx;    // group records (see GroupRecords), gx_stride words each; of the
+                           // integral form the flip masks alone, [G][2]
+    int gx_stride;
     const uint64_t *gsec;  // [G][2] flip mask compressed to (alpha bits, beta bits)
     const uint32_t *ghm;   // [G][2] (linear hash of X, sector key)
     const uint32_t *goff;  // [G + 1] term offsets
-    const uint64_t *tz;    // [T][2] Z masks
+    const uint64_t *tz;    // [..][2] Z masks of the general groups' terms (group 0 first)
+    const uint8_t *tcode;  // [T] flips in the Z mask of a tabulated group's term
     const double *tc;      // [T] folded coefficients
-    const float *tc32;     // [T][2] coefficients as FP32 (hi, lo) pairs
+    const double *occ;     // occupation rows of general groups
     const uint32_t *hr;    // [128] linear-hash words
     const double *sc_h1;   // integral form: h_pq [K][K]
     const double *sc_eri;  // integral form: (pq|rs), 8-fold packed by compound index
@@ -47,7 +50,10 @@ struct DevTable {
     int enum_ok;           // every in-sector group is a single or double excitation
     int k_alpha, k_beta;   // qubits per spin
     const uint8_t *spin_q; // [128]: alpha qubits at [0, k_alpha), beta at [64, 64 + k_beta)
-    const uint32_t *gh;    // group index slots (0xFFFFFFFF = empty)
+    // group index slots: group | min(terms, 255) << 32 | low 24 bits of its
+    // hash << 40 (all ones = empty); of the integral form 32-bit group
+    // numbers (0xFFFFFFFF = empty)
+    const void *gh;
     uint32_t gh_shift;     // 32 - log2(slots)
     const uint8_t *qcls;   // [128] class of each qubit (filter partitions)
     // the X = 0 group in occupation form (when its Z strings have at most two

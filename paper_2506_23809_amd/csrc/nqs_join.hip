@@ -514,7 +514,8 @@ __device__ __forceinline__ bool join_hit(const DevTable &tab, const Key<W> &x, c
     // any pair within the distance bound is a candidate (in a batch that
     // spans several sectors also spin-changing ones), so the group index
     // decides in the integral form too
-    const int64_t g = group_find<W>(tab, linear_hash<W>(d, tab.hr), d);
+    uint32_t cnt = 0;
+    const int64_t g = group_find<W, SCV>(tab, linear_hash<W>(d, tab.hr), d, &cnt);
     if constexpr (DUMP) {
         if (hit_idx && g >= 0) hit_idx[i * tab.n_groups + g] = j;
     }
@@ -526,13 +527,13 @@ __device__ __forceinline__ bool join_hit(const DevTable &tab, const Key<W> &x, c
             (void)row;
             hsum = sc_element<W>(tab, x, y);
         } else {
-            hsum = group_sum<W, DUMP>(tab, g, x, row, terms);
+            hsum = group_sum<W, DUMP>(tab, g, x, row, terms, cnt);
         }
         const double2 rat = amp_ratio_f64(log_amp[j] - la, phase[j] - ph);
         re += hsum * rat.x;
         im += hsum * rat.y;
     } else {
-        const AccF32 hs = group_sum_f32<W>(tab, g, x, terms);
+        const AccF32 hs = group_sum_f32<W>(tab, g, x, terms, cnt);
         float rr, ri;
         ratio_f32(log_amp[j] - la, phase[j] - ph, rr, ri);
         const float pre = hs.s * rr, pim = hs.s * ri;

@@ -179,7 +179,7 @@ __device__ __forceinline__ void lookup_item(
         if (lane < static_cast<int>(m)) {
             Key<W> xp;
 #pragma unroll
-            for (int q = 0; q < W; ++q) xp.w[q] = xl.w[q] ^ tab.gx[2 * g + q];
+            for (int q = 0; q < W; ++q) xp.w[q] = xl.w[q] ^ group_x<W>(tab, g, q);
             const uint32_t h = hxl ^ tab.ghm[2 * g];
             const int32_t j = hash_find<W>(sc.skey, sc.sidx, sc.slot_mask,
                                            slot_of(h, sc.slot_shift) << bucket_log2(W), xp);
@@ -578,7 +578,8 @@ __device__ __forceinline__ void enum_candidate(
                                    slot_of(e.y, sc.slot_shift) << bucket_log2(W), xp);
     if (j < 0) return;
     int64_t g = -1;
-    if (!SCV || DUMP) g = group_find<W>(tab, e.y ^ hx, X);
+    uint32_t terms = 0;
+    if (!SCV || DUMP) g = group_find<W, SCV>(tab, e.y ^ hx, X, &terms);
     if constexpr (DUMP) {
         if (hit_idx && g >= 0) hit_idx[idx * tab.n_groups + g] = j;
     }
@@ -592,7 +593,7 @@ __device__ __forceinline__ void enum_candidate(
             (void)row;
             hsum = sc_element<W>(tab, x, xp);
         } else {
-            hsum = group_sum<W, DUMP>(tab, g, x, row, &cnt.terms);
+            hsum = group_sum<W, DUMP>(tab, g, x, row, &cnt.terms, terms);
         }
         // (inline: this kernel's occupancy is set by its LDS, and a call
         // would only add a stack)
@@ -602,7 +603,7 @@ __device__ __forceinline__ void enum_candidate(
         c.re = hsum * (mag * cs);
         c.im = hsum * (mag * sn);
     } else {
-        const AccF32 hs = group_sum_f32<W>(tab, g, x, &cnt.terms);
+        const AccF32 hs = group_sum_f32<W>(tab, g, x, &cnt.terms, terms);
         float rr, ri;
         ratio_f32(log_amp[j] - la, phase[j] - ph, rr, ri);
         c.pre = hs.s * rr;
@@ -1975,8 +1976,9 @@ __device__ __forceinline__ int stage_diagonal(const DevTable &tab, uint64_t *dz,
         if constexpr (P == NQS_FP64) {
             dc[k] = tab.tc[t0 + k];
         } else {
-            const float2 cc = make_float2(tab.tc32[2 * static_cast<size_t>(t0 + k)],
-                                          tab.tc32[2 * static_cast<size_t>(t0 + k) + 1]);
+            const double c = tab.tc[t0 + k];
+            const float hi = static_cast<float>(c);
+            const float2 cc = make_float2(hi, static_cast<float>(c - static_cast<double>(hi)));
             dc[k] = *reinterpret_cast<const double *>(&cc);
         }
     }

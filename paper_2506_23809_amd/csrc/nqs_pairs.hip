@@ -36,9 +36,9 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 constexpr int kPairsThreads = 512;
 constexpr int kPairsWaves = kPairsThreads / 64;
 constexpr int kPairsQueue = 128;  // entries per queue and wave (64 are taken at a time)
-// Groups of more terms than this go through the queue of long groups: the
-// double excitations of a molecule have 4 or 6 terms, its single
-// excitations 2 n_qubits - 2.
+// Groups of more terms than this go through the queue of long groups (the
+// double excitations of a molecule have 4 or 6 terms in one record, its
+// single excitations 2 n_qubits - 2 and an occupation row).
 constexpr uint32_t kShortTerms = 12;
 
 struct alignas(16) PairRec {
@@ -171,8 +171,8 @@ __global__ __launch_bounds__(kPairsThreads) void pairs_kernel(
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     };
     // <x|H|y> psi(y) / psi(x) of a pair whose group is g
-    auto evaluate = [&](const PairRec &x, const PairRec &y, int64_t i, int64_t g, double &re,
-                        double &im) {
+    auto evaluate = [&](const PairRec &x, const PairRec &y, int64_t i, int64_t g, uint32_t cnt,
+                        double &re, double &im) {
         const Key<W> xk = rec_key<W>(x);
         if constexpr (P == NQS_FP64) {
             double h;
@@ -180,13 +180,13 @@ __global__ __launch_bounds__(kPairsThreads) void pairs_kernel(
                 h = sc_element<W>(tab, xk, rec_key<W>(y));
             } else {
                 uint32_t *row = (DUMP && sign_bits) ? sign_bits + i * sign_words : nullptr;
-                h = group_sum<W, DUMP>(tab, g, xk, row, &n_term);
+                h = group_sum<W, DUMP>(tab, g, xk, row, &n_term, cnt);
             }
             const double2 rat = amp_ratio_f64(y.la - x.la, y.ph - x.ph);
             re = h * rat.x;
             im = h * rat.y;
         } else {
-            const AccF32 h = group_sum_f32<W>(tab, g, xk, &n_term);
+            const AccF32 h = group_sum_f32<W>(tab, g, xk, &n_term, cnt);
             float rr, ri;
             ratio_f32(y.la - x.la, y.ph - x.ph, rr, ri);
             const float pre = h.s * rr, pim = h.s * ri;
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(kPairsThreads) void pairs_kernel(
         if (on) {
             const uint2 e = me.lq[lane];
             x = e.x & 31u;
-            evaluate(xs[x], rec[e.x >> 5], x0 + x, e.y, re, im);
+            evaluate(xs[x], rec[e.x >> 5], x0 + x, e.y, 0u, re, im);
         }
         deposit(on, x, re, im);
     };
@@ -233,16 +233,25 @@ __global__ __launch_bounds__(kPairsThreads) void pairs_kernel(
                     latch(sc.err, NQS_E_DUPLICATE);
                 } else {
                     ++n_probe;
-                    g = group_find<W>(tab, linear_hash<W>(d, hr), d);
+                    uint32_t cnt = 0;
+                    if constexpr (SCV && !DUMP) {
+                        // the flip table: every single and double that keeps
+                        // the parity of both spin counts
+                        int pa = __popcll(d.w[0] & tab.spin_a0);
+                        if constexpr (W == 2) pa += __popcll(d.w[W - 1] & tab.spin_a1);
+                        g = (pop == 2 || pop == 4) && (pa & 1) == 0 ? 0 : -1;
+                    } else {
+                        g = group_find<W, SCV>(tab, linear_hash<W>(d, hr), d, &cnt);
+                    }
                     if constexpr (DUMP) {
                         if (hit_idx && g >= 0)
                             hit_idx[i * tab.n_groups + g] = static_cast<int32_t>(j);
                     }
                     if (g >= 0) {
                         ++n_hit;
-                        later = SCV ? pop == 2 : tab.goff[g + 1] - tab.goff[g] > kShortTerms;
+                        later = SCV ? pop == 2 : cnt > kShortTerms;
                         now = !later;
-                        if (now) evaluate(xs[x], y, i, g, re, im);
+                        if (now) evaluate(xs[x], y, i, g, cnt, re, im);
                     }
                 }
             }

@@ -12,6 +12,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <numeric>
 
 #include "../../include/nqs.h"
@@ -138,12 +139,15 @@ int build_table(int n_qubits, int64_t n_terms, const uint64_t *x, const uint64_t
     // stable order by (X hi, X lo, Z hi, Z lo): equal strings keep input order
     std::vector<int64_t> ord(static_cast<size_t>(n_terms));
     std::iota(ord.begin(), ord.end(), int64_t(0));
-    std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) {
+    const auto before = [&](int64_t a, int64_t b) {
         if (x[2 * a + 1] != x[2 * b + 1]) return x[2 * a + 1] < x[2 * b + 1];
         if (x[2 * a] != x[2 * b]) return x[2 * a] < x[2 * b];
         if (z[2 * a + 1] != z[2 * b + 1]) return z[2 * a + 1] < z[2 * b + 1];
         return z[2 * a] < z[2 * b];
-    });
+    };
+    // (terms often come in this order)
+    if (!std::is_sorted(ord.begin(), ord.end(), before))
+        std::stable_sort(ord.begin(), ord.end(), before);
 
     const LinearHash lh;
     T.tz.reserve(2 * static_cast<size_t>(n_terms));
@@ -367,6 +371,85 @@ void build_diag_tiles(const HostTable &T, std::vector<int8_t> *out, double *scal
                 }
             }
         }
+    }
+}
+
+void build_group_records(const HostTable &T, GroupRecords *out) {
+    const int W = T.words, nq = T.n_qubits;
+    out->rec.assign(static_cast<size_t>(T.n_groups) * kGroupWords, 0);
+    out->codes.assign(static_cast<size_t>(T.n_terms), 0);
+    out->z.clear();
+    out->rows.clear();
+    // odd[c & p] for four-bit c, p: parity by table (the host build has no
+    // popcount instruction)
+    static const uint8_t odd[16] = {0, 1, 1, 0, 1, 0, 0, 1, 1, 0, 0, 1, 0, 1, 1, 0};
+    for (int64_t g = 0; g < T.n_groups; ++g) {
+        const uint64_t x[2] = {T.gx[2 * g], T.gx[2 * g + 1]};
+        uint64_t *rec = &out->rec[static_cast<size_t>(g) * kGroupWords];
+        uint64_t *value = rec + 2 * W;
+        for (int q = 0; q < W; ++q) rec[q] = x[q];
+        const int64_t t0 = T.goff[g], t1 = T.goff[g + 1];
+        const uint64_t *z = &T.tz[2 * t0];
+        // the flips, in qubit order (at most five are told apart)
+        int flip[5], m = 0;
+        for (int q = 0; q < 2; ++q)
+            for (uint64_t v = x[q]; v && m < 5; v &= v - 1) flip[m++] = 64 * q + __builtin_ctzll(v);
+        // which flips the string of term t has
+        auto code_of = [&](int64_t t) {
+            unsigned c = 0;
+            for (int k = 0; k < m; ++k)
+                c |= static_cast<unsigned>((z[2 * t + (flip[k] >> 6)] >> (flip[k] & 63)) & 1ull) << k;
+            return c;
+        };
+        const uint64_t b0 = z[0] & ~x[0], b1 = z[1] & ~x[1];
+        bool alike = m >= 1 && m <= 4;
+        for (int64_t t = 1; alike && t < t1 - t0; ++t)
+            alike = (z[2 * t] & ~x[0]) == b0 && (z[2 * t + 1] & ~x[1]) == b1;
+        if (alike) {
+            rec[W] = b0;
+            if (W == 2) rec[W + 1] = b1;
+            double s[4] = {0.0, 0.0, 0.0, 0.0};
+            const unsigned pat[4] = {0u, m == 4 ? 10u : 2u, m == 4 ? 12u : 4u, 6u};
+            for (int64_t t = 0; t < t1 - t0; ++t) {
+                const unsigned c = code_of(t);
+                out->codes[t0 + t] = static_cast<uint8_t>(c);
+                const double v = T.tc[t0 + t];
+                for (int i = 0; i < 4; ++i) s[i] += odd[c & pat[i]] ? -v : v;
+            }
+            std::memcpy(value, s, sizeof s);
+            continue;
+        }
+        rec[W - 1] |= kGroupGeneral;
+        value[2] = 0;
+        value[3] = out->z.size() / 2;
+        out->z.insert(out->z.end(), T.tz.begin() + 2 * t0, T.tz.begin() + 2 * t1);
+        if (m < 1 || m > 2 || t1 - t0 < 8) continue;
+        // the common base: the majority of each qubit outside the flips
+        int have[128] = {};
+        for (int64_t t = 0; t < t1 - t0; ++t)
+            for (int q = 0; q < 2; ++q)
+                for (uint64_t v = z[2 * t + q] & ~x[q]; v; v &= v - 1) ++have[64 * q + __builtin_ctzll(v)];
+        uint64_t base[2] = {0, 0};
+        for (int q = 0; q < nq; ++q)
+            if (2 * have[q] > t1 - t0) base[q >> 6] |= 1ull << (q & 63);
+        bool form = true;
+        std::vector<long double> row(2 * static_cast<size_t>(nq + 2), 0.0L);
+        for (int64_t t = 0; form && t < t1 - t0; ++t) {
+            const uint64_t d0 = (z[2 * t] & ~x[0]) ^ base[0], d1 = (z[2 * t + 1] & ~x[1]) ^ base[1];
+            form = (d0 & (d0 - 1)) == 0 && (d1 & (d1 - 1)) == 0 && (d0 == 0 || d1 == 0);
+            const int at = d0 ? __builtin_ctzll(d0) : (d1 ? 64 + __builtin_ctzll(d1) : -1);
+            for (int b = 0; b < 2 && form; ++b) {
+                // c (-1)^{x_r} = c - 2 c n_r
+                long double *r = &row[static_cast<size_t>(b) * (nq + 2)];
+                const long double c = odd[code_of(t) & (b ? 2u : 0u)] ? -T.tc[t0 + t] : T.tc[t0 + t];
+                r[0] += c;
+                if (at >= 0) r[1 + at] -= 2.0L * c;
+            }
+        }
+        if (!form) continue;
+        for (int q = 0; q < W; ++q) rec[W + q] = base[q];
+        value[2] = 1 + out->rows.size() / (2 * static_cast<size_t>(nq + 2));
+        for (const long double v : row) out->rows.push_back(static_cast<double>(v));
     }
 }
 

@@ -92,6 +92,39 @@ constexpr int kDiagLimbs = 2 * kDiagDigits;  // byte planes
 constexpr int kDiagBits = 59;
 void build_diag_tiles(const HostTable &T, std::vector<int8_t> *out, double *scale);
 
+// The groups as the kernels read them: one 64-byte record per group (W mask
+// words, eight 64-bit words in all),
+//   X [W], base [W], value [4].
+// A group of at most four flips whose Z strings agree outside the flips
+// (base; every double excitation) is tabulated: the strings differ only in
+// an even number of flipped qubits, so up to the sign (-1)^{popc(base & x)}
+// <x|H|x ^ X> depends on the bits of x at the flips alone and is the same for
+// their complement.  value[i] is the sum, in term order, where the second
+// and third flip (in qubit order) differ from the first as bits 0 and 1 of i
+// say and, with four flips, the fourth so that the four bits have even
+// parity (what a sample of the same sector as x ^ X has; other samples sum
+// the terms).  A general group has kGroupGeneral set in its last X word;
+// value[2] and value[3] then hold integers: 1 + its occupation row (0: none)
+// and the place of its first Z string in z.
+//   codes [T]: of a term of a tabulated group, which flips its string has
+//   z [..][2]: the strings of the general groups, in term order
+//   rows [..][2][nq + 2]: the occupation rows of general groups of one or
+//   two flips whose strings outside the flips differ from a common base in
+//   at most one qubit (single excitations): up to the sign of that base the
+//   group's sum is row[0] + sum of row[1 + q] over the occupied q, the first
+//   row where the two flips are alike, the second where they differ (the
+//   last entry is 0).  Half the additions of the term form and a tenth of
+//   its bytes.
+constexpr uint64_t kGroupGeneral = 1ull << 63;
+constexpr int kGroupWords = 8;
+struct GroupRecords {
+    std::vector<uint64_t> rec;
+    std::vector<uint8_t> codes;
+    std::vector<uint64_t> z;
+    std::vector<double> rows;
+};
+void build_group_records(const HostTable &T, GroupRecords *out);
+
 // Sector key: half of popc(X & alpha) | half of popc(X & beta) << 8, or
 // kSectorNeverKey when either popcount is odd (the flip always leaves the
 // sector).
