@@ -214,7 +214,7 @@ struct DevScratch {
     uint32_t *jcnt;             // [parts] entries per partition
     unsigned long long *jreg;   // [parts][join_cap] each partition's entries, scatter order:
                                 // fingerprint << 56 | (key & (2^join_lshift - 1)) << 32 | sample
-    // entries by partition, then bucket, then fingerprint, then sample index
+    // entries by partition, then bucket, then fingerprint (large buckets whole)
     uint32_t *jent;             // [blocks * n] the entry's sample
     unsigned long long *jrange; // [blocks * n] first entry of the entry's group (its bucket's
                                 // members of its fingerprint) | group size << 32 | block << 48

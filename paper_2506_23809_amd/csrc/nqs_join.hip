@@ -18,7 +18,7 @@
 // partitions by their high bits (about a thousand entries each).  A tile of
 // samples counts its entries per partition in LDS and reserves its share
 // of each partition with one atomic; the entries are then placed, each
-// partition is sorted in LDS by (bucket, content fingerprint, sample), and
+// partition is sorted in LDS by (bucket, content fingerprint), and
 // the start and size of each entry's group (its bucket's members with its
 // fingerprint: hash-colliding contents mostly fall apart) are written beside
 // the entries.  The pair kernel then takes one lane per entry.
@@ -31,10 +31,12 @@
 // insertion, the enumeration and the streaming kernels of the same launch
 // stand down; otherwise those run and the pair kernel returns at once.
 //
-// Determinism: a partition is sorted by sample index within each group, so
-// each sample's hits are added in a fixed order (one partial per block,
-// partners in index order), and the finish kernel adds the block partials
-// in block order.
+// Determinism: a group's members come in whatever order the placing atomics
+// gave, so each sample's hits are added as double-doubles (one partial per
+// block, whose bits do not depend on that order), and the finish kernel adds
+// the block partials in block order.  (Ordering them instead took a bitonic
+// sort wherever a bucket was large: 92 us of the 40-qubit batch of 65,536
+// samples.)
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -51,9 +53,8 @@ constexpr int kJoinGroupThreads = 1024;  // tile kernels
 constexpr int kJoinPairThreads = 256;
 constexpr int kJoinPairPer = 4;  // entries per lane of the pair kernel, at most
 constexpr int kJoinSortThreads = 512;
-// Largest bucket ranked by a pass over its members; a partition with a
-// larger one is bitonic-sorted whole.
-constexpr unsigned long long kJoinRankMax = 64;
+// Largest bucket split by a pass over its members; a larger one stays whole.
+constexpr uint32_t kJoinRankMax = 64;
 constexpr int kJoinMaxParts = 8192;      // partitions of any planned launch
 constexpr int kJoinMaxLocal = 2048;      // buckets per partition (2^join_lshift)
 constexpr int kJoinTiles = 128;          // tiles of the grouping kernels, at most
@@ -271,7 +272,7 @@ __global__ __launch_bounds__(kJoinGroupThreads) void join_scatter_kernel(
 }
 
 // One partition (c entries, at most kJoinPartCap) ordered by (bucket,
-// content fingerprint, sample); thread 0 writes its statistics.
+// content fingerprint); thread 0 writes its statistics.
 template <int W>
 __device__ __forceinline__ void join_sort_partition(const DevTable &tab, const DevScratch &sc,
                                                     const uint64_t *__restrict__ samples, int p,
@@ -293,12 +294,8 @@ __device__ __forceinline__ void join_sort_partition(const DevTable &tab, const D
     // bucket starts (exclusive scan of the counts), packed with the sizes
     const int per = (L + blockDim.x - 1) / blockDim.x;
     const int u0 = threadIdx.x * per;
-    unsigned long long own = 0, mx = 0;
-    for (int u = u0; u < u0 + per && u < L; ++u) {
-        const unsigned long long v = cnt[u];
-        own += v;
-        mx = v > mx ? v : mx;
-    }
+    unsigned long long own = 0;
+    for (int u = u0; u < u0 + per && u < L; ++u) own += cnt[u];
     unsigned long long total;
     unsigned long long run = block_exclusive_scan(own, &total);
     for (int u = u0; u < u0 + per && u < L; ++u) {
@@ -306,14 +303,7 @@ __device__ __forceinline__ void join_sort_partition(const DevTable &tab, const D
         cnt[u] = static_cast<uint32_t>(run) | (v << 16);
         run += v;
     }
-    // the partition's largest bucket (also decides the ordering method
-    // below)
-    unsigned long long none = 0;
-    block_sum_max(none, mx);
-    __shared__ unsigned long long s_mx;
-    if (threadIdx.x == 0) s_mx = mx;
     __syncthreads();
-    const unsigned long long mx_all = s_mx;
     // each entry at its bucket's next place: the low half of cnt[] serves as
     // the cursor (it ends at the bucket's end, below 2^16)
     for (uint32_t u = threadIdx.x; u < c; u += blockDim.x) {
@@ -324,54 +314,30 @@ __device__ __forceinline__ void join_sort_partition(const DevTable &tab, const D
         fpr[at] = static_cast<uint8_t>(e >> kJoinFpShift);
     }
     __syncthreads();
-    // large buckets (clustered samples: few distinct block contents): sort
-    // the whole partition (bitonic, 4-byte keys in LDS) instead of ranking
-    // each entry by a pass over its bucket, which would be quadratic
-    const bool big = mx_all > kJoinRankMax;
-    if (big) {
-        uint32_t P2 = 2;
-        while (P2 < c) P2 <<= 1;
-        for (uint32_t u = c + threadIdx.x; u < P2; u += blockDim.x) buf[u] = 0xFFFFFFFFu;
-        for (uint32_t k = 2; k <= P2; k <<= 1) {
-            for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-                __syncthreads();
-                for (uint32_t t = threadIdx.x; t < (P2 >> 1); t += blockDim.x) {
-                    // the t-th index with bit j clear, and its partner
-                    const uint32_t a = ((t & ~(j - 1u)) << 1) | (t & (j - 1u)), l = a + j;
-                    const uint32_t va = buf[a], vl = buf[l];
-                    if ((va > vl) == ((a & k) == 0)) {
-                        buf[a] = vl;
-                        buf[l] = va;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-    }
     const int blk = p >> (sc.join_log2m - sc.join_lshift);
     const uint4 *__restrict__ src = reinterpret_cast<const uint4 *>(samples);
     uint4 *keys = reinterpret_cast<uint4 *>(sc.jkeys);
     // each entry's place: its bucket's start, the members of its bucket with
-    // a smaller fingerprint, then those of its own fingerprint with a smaller
-    // sample index; its range is its fingerprint group (the whole bucket for
-    // a bitonic-sorted partition)
+    // a smaller fingerprint, then those of its own fingerprint before it;
+    // its range is its fingerprint group.  A large bucket (samples that share
+    // the block's contents: nothing to split, and the pass over its members
+    // would be quadratic) stays whole and as placed.
     unsigned long long pairs = 0, largest = 0;
     for (uint32_t u = threadIdx.x; u < c; u += blockDim.x) {
         const uint32_t v = buf[u];
         const uint32_t loc = v >> 21, me = v & 0x1FFFFFu;
         const uint32_t r = cnt[loc];
         const uint32_t m = r >> 16, bs = (r & 0xFFFFu) - m;
-        uint32_t rank = 0, gs = bs, gm = m;
-        if (big) {
-            rank = u - bs;  // sorted: the place in the bucket is the offset
-        } else if (m >= 2) {
+        uint32_t rank = u - bs, gs = bs, gm = m;
+        if (m >= 2 && m <= kJoinRankMax) {
             const uint32_t f = fpr[u];
             uint32_t below = 0, same = 0;
+            rank = 0;
             for (uint32_t q = bs; q < bs + m; ++q) {
-                const uint32_t fq = fpr[q], mq = buf[q] & 0x1FFFFFu;
+                const uint32_t fq = fpr[q];
                 below += fq < f ? 1u : 0u;
                 same += fq == f ? 1u : 0u;
-                rank += (fq < f || (fq == f && mq < me)) ? 1u : 0u;
+                rank += (fq < f || (fq == f && q < u)) ? 1u : 0u;
             }
             gs = bs + below;
             gm = same;
@@ -455,20 +421,19 @@ __device__ __forceinline__ void join_decide(const DevTable &tab, const DevScratc
 }
 
 // One block per partition: its entries ordered by (bucket, content
-// fingerprint, sample) and written back, each with the range of its group
-// (the members of its bucket with its fingerprint), its block and its bit
-// string; the partition's sum of squared group sizes and largest group.  A
-// counting sort by bucket (LDS counts, their scan, then each entry at its
-// bucket's start plus a cursor in the same word) groups the buckets; an
-// entry's place inside its bucket is then the number of members with a
-// smaller content fingerprint (which the scatter put in the entry's top
-// byte), or the same one and a smaller sample index (a pass over the
-// bucket, as long as the pair kernel's).  Buckets of hash-colliding
-// contents thus split, and the pair kernel tests only the pairs whose
-// contents agree up to 2^-8.  LDS holds 4 bytes per entry (bucket << 21 |
-// sample) and its fingerprint byte, so that several blocks share a CU.  A partition whose largest bucket needs the bitonic sort keeps
-// whole buckets as its groups.  A partition of more than kJoinPartCap
-// entries is only flagged (the join then does not run).
+// fingerprint) and written back, each with the range of its group (the
+// members of its bucket with its fingerprint), its block and its bit string;
+// the partition's sum of squared group sizes and largest group.  A counting
+// sort by bucket (LDS counts, their scan, then each entry at its bucket's
+// start plus a cursor in the same word) groups the buckets; an entry's place
+// inside its bucket is then the number of members with a smaller content
+// fingerprint (which the scatter put in the entry's top byte), or the same
+// one and an earlier place (a pass over the bucket, as long as the pair
+// kernel's).  Buckets of hash-colliding contents thus split, and the pair
+// kernel tests only the pairs whose contents agree up to 2^-8.  LDS holds 4
+// bytes per entry (bucket << 21 | sample) and its fingerprint byte, so that
+// several blocks share a CU.  A partition of more than kJoinPartCap entries
+// is only flagged (the join then does not run).
 template <int W>
 __global__ __launch_bounds__(kJoinSortThreads) void join_sort_kernel(
     DevTable tab, DevScratch sc, const uint64_t *__restrict__ samples) {
@@ -509,8 +474,7 @@ __device__ __forceinline__ bool join_hit(const DevTable &tab, const Key<W> &x, c
                                          const double *__restrict__ phase,
                                          int32_t *__restrict__ hit_idx,
                                          uint32_t *__restrict__ sign_bits, int64_t sign_words,
-                                         unsigned long long *terms, double &re, double &im,
-                                         AccF32 &ar, AccF32 &ai) {
+                                         unsigned long long *terms, Acc2 &re, Acc2 &im) {
     // any pair within the distance bound is a candidate (in a batch that
     // spans several sectors also spin-changing ones), so the group index
     // decides in the integral form too
@@ -530,15 +494,15 @@ __device__ __forceinline__ bool join_hit(const DevTable &tab, const Key<W> &x, c
             hsum = group_sum<W, DUMP>(tab, g, x, row, terms, cnt);
         }
         const double2 rat = amp_ratio_f64(log_amp[j] - la, phase[j] - ph);
-        re += hsum * rat.x;
-        im += hsum * rat.y;
+        re.add(hsum * rat.x);
+        im.add(hsum * rat.y);
     } else {
         const AccF32 hs = group_sum_f32<W>(tab, g, x, terms, cnt);
         float rr, ri;
         ratio_f32(log_amp[j] - la, phase[j] - ph, rr, ri);
         const float pre = hs.s * rr, pim = hs.s * ri;
-        ar.add(pre, fmaf(hs.s, rr, -pre) + hs.c * rr);
-        ai.add(pim, fmaf(hs.s, ri, -pim) + hs.c * ri);
+        re.add(static_cast<double>(pre) + static_cast<double>(fmaf(hs.s, rr, -pre) + hs.c * rr));
+        im.add(static_cast<double>(pim) + static_cast<double>(fmaf(hs.s, ri, -pim) + hs.c * ri));
     }
     return true;
 }
@@ -546,7 +510,7 @@ __device__ __forceinline__ bool join_hit(const DevTable &tab, const Key<W> &x, c
 // One lane per entry with partners (block b, sample i; each wave gathers
 // them from its per x 64 consecutive entries, so that with per > 1 lanes
 // are not spent on the many entries alone in their group): the partners of
-// i in its group, in index order; with a hit, its partial sum goes to
+// i in its group; with a hit, its partial sum goes to
 // part[b][i] and bit b * n + i of the hit map is set (the finish reads only
 // flagged partials).  The first build_blocks blocks are the sample-hash
 // build of the same launch instead (its checks always; its insertion when
@@ -595,9 +559,9 @@ __global__ __launch_bounds__(kJoinPairThreads) void join_pair_kernel(
         const int64_t e = static_cast<int64_t>(b) * n + i;
         if (m >= 2) {
             const Key<W> x = load_key<W>(sc.jkeys, p);
-            double re = 0.0, im = 0.0, la = 0.0, ph = 0.0;
+            double la = 0.0, ph = 0.0;
             bool have_psi = false;
-            AccF32 ar, ai;
+            Acc2 re, im;
             // one candidate: distance, first agreeing block, then the hit
             auto visit = [&](uint32_t q, const Key<W> &y) {
                 if (q == static_cast<uint32_t>(p)) return;
@@ -632,10 +596,10 @@ __global__ __launch_bounds__(kJoinPairThreads) void join_pair_kernel(
                     have_psi = true;
                 }
                 if (join_hit<W, DUMP, P, SCV>(tab, x, y, d, i, j, la, ph, log_amp, phase, hit_idx,
-                                              sign_bits, sign_words, &n_term, re, im, ar, ai))
+                                              sign_bits, sign_words, &n_term, re, im))
                     ++n_hit;
             };
-            // partners in index order; one-word bit strings four at a time
+            // one-word bit strings four at a time
             // (large buckets wait on these loads; two-word strings would
             // cost the kernel a wave per SIMD in registers)
             uint32_t q = bs;
@@ -653,13 +617,8 @@ __global__ __launch_bounds__(kJoinPairThreads) void join_pair_kernel(
             for (; q < bs + m; ++q) visit(q, load_key<W>(sc.jkeys, q));
             n_cand += m - 1;
             if (n_hit) {
-                double2 sum;
-                if constexpr (P == NQS_FP64) {
-                    sum = make_double2(re, im);
-                } else {
-                    sum = make_double2(ar.value(), ai.value());
-                }
-                *reinterpret_cast<double2 *>(sc.part + 2 * e) = sum;
+                *reinterpret_cast<double2 *>(sc.part + 2 * e) =
+                    make_double2(re.value(), im.value());
                 atomicOr(&sc.jhit[e >> 5], 1u << (e & 31));
             }
         }
