@@ -336,6 +336,12 @@ hipError_t launch_join_pairs(const DevTable &tab, const DevScratch &sc, const ui
                              const double *phase, int64_t n, int precision, int32_t *hit_idx,
                              uint32_t *sign_bits, int64_t sign_words, hipStream_t st);
 
+// Batches above this many samples take 64 samples x a block instead of 32:
+// half the operand traffic per pair once that still gives every compute unit
+// four blocks (65,536 spread samples at 100 qubits: 234 us against 358;
+// 37,843 gathered ones at 40 qubits 625 against 682; below it the longer
+// tail costs more, 20,001 gathered ones at 100 qubits 477 against 411).
+constexpr int64_t kPairsWide = 32768;
 // The comparison of all pairs: scratch, the launch that clears the counters,
 // checks the samples and lays them out, and the pair kernel.
 size_t pairs_scratch_bytes(const DevTable &tab, int64_t n);

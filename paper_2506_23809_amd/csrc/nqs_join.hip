@@ -402,7 +402,8 @@ __device__ __forceinline__ void join_decide(const DevTable &tab, const DevScratc
     const bool fits = sc.jctl[kJoinCtlOver] == 0ull;
     bool chosen = fits && (sc.join_force != 0 || cost < alt);
     if (sc.pairs == 2) {
-        // beside the comparison of all pairs (0.09 ps a pair and 8 us) the
+        // beside the comparison of all pairs (0.09 ps a pair, 0.055 in wide
+        // blocks, and 8 us) the
         // grouping is spent either way: what counts is the pair kernel, about
         // two probes a candidate and 18 an entry (79 us for 86.9 M candidates
         // at 40 qubits, 11 us for 1.3 M entries at 100), and the serial chain
@@ -413,7 +414,8 @@ __device__ __forceinline__ void join_decide(const DevTable &tab, const DevScratc
         // (100 qubits, 20,001, 307 in a group)
         const double dn = static_cast<double>(n);
         const double chain = (tab.n_qubits <= 63 ? 2.1e5 : 1.5e6) * static_cast<double>(m);
-        chosen = fits && 2.0 * cand + 18.0 * entries + chain < 0.19 * dn * dn + 1.7e7;
+        chosen = fits && 2.0 * cand + 18.0 * entries + chain <
+                             (n > kPairsWide ? 0.117 : 0.19) * dn * dn + 1.7e7;
     }
     sc.jctl[kJoinCtlCost] = q;
     sc.jctl[kJoinCtlMax] = m;

@@ -2590,19 +2590,20 @@ constexpr int64_t kPairsDirect = 8192;
 // Whether comparing all pairs of n samples takes less time than the
 // strategy beside the pair join: the enumeration of a half-filled sector, or
 // streaming.  Picoseconds on MI355X: a pair 0.09 (11.5 us for 8,192 samples
-// at 100 qubits, 5 of them the launch), a connected pair 100 against 300 of
-// the enumeration (37,843 gathered samples at 40 qubits with 17 M hits: 1.85
-// ms against 3.31), a lookup of the enumeration 0.47 (70.9 ms for 1.5 10^11)
+// at 100 qubits, 5 of them the launch) or 0.055 in wide blocks (234 us for
+// 65,536), a connected pair 35 against 150 of the enumeration (37,843
+// gathered samples at 40 qubits with 17 M hits: 0.62 ms of kernel; 24 qubits,
+// 100,001 samples, 34 M hits: 1.63 against 7.8), a lookup of the enumeration 0.47 (70.9 ms for 1.5 10^11)
 // and 6 10^7 for the hash it needs, a streamed pair 1.2 (20,000 groups past
 // 10,007 samples: 240 us); a near pair that the group index decides 2.
 bool pairs_cheaper(const DevTable &tab, int64_t n) {
     // (the pair kernel packs a sample's index in 27 bits)
     if (n > kJoinMaxSamples) return false;
     const double dn = static_cast<double>(n);
-    const double cost = dn * dn * (0.09 + 2.0 * tab.near_share);
+    const double cost = dn * dn * ((n > kPairsWide ? 0.055 : 0.09) + 2.0 * tab.near_share);
     if (!tab.enum_ok) return cost < 1.2 * dn * static_cast<double>(tab.n_groups) + 4.0e7;
     const double hits = dn * tab.half_flips * std::fmin(1.0, dn / tab.half_states);
-    return cost + 100.0 * hits < 0.47 * dn * tab.half_flips + 300.0 * hits + 6.0e7;
+    return cost + 35.0 * hits < 0.47 * dn * tab.half_flips + 150.0 * hits + 6.0e7;
 }
 }  // namespace
 
@@ -2668,10 +2669,11 @@ EvalLaunch plan_eval(const DevTable &tab, int64_t n, bool dump, const Tuning *tu
     if (want == kStrategyAuto && pairs_cheaper(tab, n)) {
         L.pairs = L.join && n > kPairsDirect ? 2 : 1;
         if (L.pairs == 1) L.join = 0;
-        // two shares of the columns where one leaves compute units idle (a
-        // share's partial takes the room of two)
+        // two shares of the columns, for more and shorter blocks (a share's
+        // partial takes the room of two): 20,001 gathered samples at 100
+        // qubits 508 us with one, 411 with two
         const int64_t room = L.join_scratch ? tab.join_blocks : 0;
-        if ((n + 31) / 32 < 2 * device_cus() && (L.n_chunks > room ? L.n_chunks : room) >= 4)
+        if ((L.n_chunks > room ? L.n_chunks : room) >= 4)
             L.pairs_split = 2;
     }
     return L;

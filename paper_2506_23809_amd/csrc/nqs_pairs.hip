@@ -118,39 +118,45 @@ __device__ __forceinline__ Key<W> rec_key(const PairRec &r) {
 
 // Shared state of one wave.
 struct PairsWave {
-    uint32_t q[kPairsQueue];       // near pairs: x of the tile | y << 5
+    uint32_t q[kPairsQueue];       // near pairs: x of the tile | y << 6
     uint2 lq[kPairsQueue];         // pairs whose group is long: the same, group
     double con[2][64];             // contributions of a batch (re, im)
-    unsigned long long own[32];    // which of them belong to each x
+    unsigned long long own[64];    // which of them belong to each x
 };
 
-// One block per 32 samples x (blockIdx.x) and share of the samples y
+// One block per 32 H samples x (blockIdx.x) and share of the samples y
 // (blockIdx.y); its waves take the tiles of y in turn.
 //
-// Bound: per 32 x 32 pairs one (W = 1) or two FP4 MFMAs of 32 cycles and
-// about ten VALU instructions where no pair is near; per near pair the
-// gathers of its record, group and terms, and the FP64 amplitude ratio.
-template <int W, bool DUMP, int P, bool SCV>
-__global__ __launch_bounds__(kPairsThreads) void pairs_kernel(
+// Bound: per 32 x 32 pairs one (W = 1) or two FP4 MFMAs of 32 cycles, about
+// ten VALU instructions where no pair is near and 1 KB W / H of operand from
+// the caches; per near pair the gathers of its record, group and values, and
+// the FP64 amplitude ratio (about 590 VALU instructions per 64 pairs).
+// Registers: 128 (four waves a SIMD); at 134 the 100-qubit form took 627 us
+// instead of 508 for 20,001 gathered samples, at 96 it spilled (600).
+template <int W, int H, bool DUMP, int P, bool SCV>
+__global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
     DevTable tab, DevScratch sc, int64_t n, const double *__restrict__ log_amp,
     const double *__restrict__ phase, int32_t *__restrict__ hit_idx,
     uint32_t *__restrict__ sign_bits, int64_t sign_words) {
     if (!pairs_chosen(sc)) return;
-    __shared__ PairRec xs[32];
+    constexpr int R = 32 * H;  // samples x of the block
+    __shared__ PairRec xs[R];
     __shared__ uint32_t hr[128];
     __shared__ PairsWave waves[kPairsWaves];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t x0 = static_cast<int64_t>(blockIdx.x) * 32;
+    const int64_t x0 = static_cast<int64_t>(blockIdx.x) * R;
     const PairRec *__restrict__ rec = reinterpret_cast<const PairRec *>(sc.prec);
-    if (threadIdx.x < 32) {
+    if (threadIdx.x < R) {
         const int64_t i = x0 + threadIdx.x;
         xs[threadIdx.x] = i < n ? rec[i] : PairRec{0, 0, 0.0, 0.0};
     }
     if (threadIdx.x < 128) hr[threadIdx.x] = tab.hr[threadIdx.x];
     __syncthreads();
     PairsWave &me = waves[wave];
-    const int comp = lane >> 5, xl = lane & 31;  // this lane sums component comp of x xl
-    Acc2 acc;
+    // the sums of x: with 32 samples lane comp 32 + xl has component comp of
+    // sample xl, with 64 lane x has both components of sample x
+    const int half = lane >> 5, xl = lane & 31;
+    Acc2 acc[H];
     unsigned long long n_probe = 0, n_hit = 0, n_term = 0;
 
     // the contributions con[.][0..63] of the lanes in valid (x: the lane's
@@ -158,15 +164,20 @@ __global__ __launch_bounds__(kPairsThreads) void pairs_kernel(
     auto deposit = [&](bool valid, uint32_t x, double re, double im) {
         me.con[0][lane] = re;
         me.con[1][lane] = im;
-        if (lane < 32) me.own[lane] = 0ull;
+        if (lane < R) me.own[lane] = 0ull;
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         if (valid) atomicOr(&me.own[x], 1ull << lane);
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        unsigned long long mine = me.own[xl];
+        unsigned long long mine = me.own[H == 1 ? xl : lane];
         while (mine) {
             const int k = __builtin_ctzll(mine);
             mine &= mine - 1;
-            acc.add(me.con[comp][k]);
+            if constexpr (H == 1) {
+                acc[0].add(me.con[half][k]);
+            } else {
+                acc[0].add(me.con[0][k]);
+                acc[1].add(me.con[1][k]);
+            }
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     };
@@ -202,8 +213,8 @@ __global__ __launch_bounds__(kPairsThreads) void pairs_kernel(
         double re = 0.0, im = 0.0;
         if (on) {
             const uint2 e = me.lq[lane];
-            x = e.x & 31u;
-            evaluate(xs[x], rec[e.x >> 5], x0 + x, e.y, 0u, re, im);
+            x = e.x & 63u;
+            evaluate(xs[x], rec[e.x >> 6], x0 + x, e.y, 0u, re, im);
         }
         deposit(on, x, re, im);
     };
@@ -215,8 +226,8 @@ __global__ __launch_bounds__(kPairsThreads) void pairs_kernel(
         double re = 0.0, im = 0.0;
         if (lane < static_cast<int>(m)) {
             e = me.q[lane];
-            x = e & 31u;
-            const int64_t i = x0 + x, j = e >> 5;
+            x = e & 63u;
+            const int64_t i = x0 + x, j = e >> 6;
             if (i != j) {
                 const PairRec y = rec[j];
                 const Key<W> xk = rec_key<W>(xs[x]), yk = rec_key<W>(y);
@@ -267,68 +278,75 @@ __global__ __launch_bounds__(kPairsThreads) void pairs_kernel(
         }
     };
 
-    // the x operand, resident; the C operand: near pairs come out positive
+    // the x operands, resident; the C operand: near pairs come out positive
     const v4i *__restrict__ ops = reinterpret_cast<const v4i *>(sc.pops);
-    v8i xo[W];
+    const int tiles = static_cast<int>((n + 31) / 32);
+    auto operand = [&](int t, int kb) {
+        const v4i o = ops[(static_cast<int64_t>(t) * W + kb) * 64 + lane];
+        return v8i{o[0], o[1], o[2], o[3], 0, 0, 0, 0};
+    };
+    v8i xo[H][W];
+    uint32_t x_in = 0;  // bits of the halves whose sample exists
 #pragma unroll
-    for (int kb = 0; kb < W; ++kb) {
-        const v4i o = ops[(static_cast<int64_t>(blockIdx.x) * W + kb) * 64 + lane];
-        xo[kb] = v8i{o[0], o[1], o[2], o[3], 0, 0, 0, 0};
+    for (int h = 0; h < H; ++h) {
+        const int t = static_cast<int>(blockIdx.x) * H + h;
+#pragma unroll
+        for (int kb = 0; kb < W; ++kb) xo[h][kb] = operand(t < tiles ? t : tiles - 1, kb);
+        if (x0 + 32 * h + xl < n) x_in |= 0xFFFFu << (16 * (H - 1 - h));
     }
     const float thr = 0.5f - static_cast<float>(tab.n_qubits - 2 * tab.max_flip);
     v16f cthr;
 #pragma unroll
     for (int r = 0; r < 16; ++r) cthr[r] = thr;
-    const bool x_in = x0 + xl < n;
-    const int tiles = static_cast<int>((n + 31) / 32);
+    // this wave's tiles: every step-th
     const int step = kPairsWaves * static_cast<int>(gridDim.y);
     int t = wave + kPairsWaves * static_cast<int>(blockIdx.y);
-    v4i next[W];
+    v8i next[W];
 #pragma unroll
-    for (int kb = 0; kb < W; ++kb) next[kb] = v4i{0, 0, 0, 0};
-    if (t < tiles) {
-#pragma unroll
-        for (int kb = 0; kb < W; ++kb) next[kb] = ops[(static_cast<int64_t>(t) * W + kb) * 64 + lane];
-    }
+    for (int kb = 0; kb < W; ++kb) next[kb] = operand(t < tiles ? t : tiles - 1, kb);
     for (; t < tiles; t += step) {
-        v16f c = cthr;
+        v16f c[H];
 #pragma unroll
-        for (int kb = 0; kb < W; ++kb) {
-            const v8i a = v8i{next[kb][0], next[kb][1], next[kb][2], next[kb][3], 0, 0, 0, 0};
-            c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, xo[kb], c, 4, 4, 0, 0, 0, 0);
-        }
-        if (t + step < tiles) {
+        for (int h = 0; h < H; ++h) {
+            c[h] = cthr;
 #pragma unroll
             for (int kb = 0; kb < W; ++kb)
-                next[kb] = ops[(static_cast<int64_t>(t + step) * W + kb) * 64 + lane];
+                c[h] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(next[kb], xo[h][kb], c[h], 4,
+                                                                       4, 0, 0, 0, 0);
         }
-        float mx = c[0];
 #pragma unroll
-        for (int r = 1; r < 15; r += 2) mx = fmaxf(fmaxf(mx, c[r]), c[r + 1]);
-        mx = fmaxf(mx, c[15]);
+        for (int kb = 0; kb < W; ++kb) next[kb] = operand(t + step < tiles ? t + step : t, kb);
+        float mx = c[0][0];
+#pragma unroll
+        for (int v = 1; v < 16 * H; v += 2) {
+            const int w = v + 1 < 16 * H ? v + 1 : v;
+            mx = fmaxf(fmaxf(mx, c[v >> 4][v & 15]), c[w >> 4][w & 15]);
+        }
         if (__ballot(mx > 0.0f) == 0ull) continue;
-        // bit 15 - r: value r is positive (lane's x = lane % 32, its y are
-        // rows 8 (r / 4) + 4 (lane / 32) + r % 4 of the tile)
+        // bit 16 H - 1 - v: value v = 16 h + r is positive (the lane's x is
+        // 32 h + lane % 32, its y row 8 (r / 4) + 4 (lane / 32) + r % 4 of
+        // the tile)
         uint32_t neg = 0;
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-            neg = (neg << 1) | (__float_as_uint(c[r]) >> 31);
-        uint32_t near = ~neg & 0xFFFFu;
-        if (!x_in) near = 0;
+        for (int v = 0; v < 16 * H; ++v)
+            neg = (neg << 1) | (__float_as_uint(c[v >> 4][v & 15]) >> 31);
+        uint32_t near = ~neg & x_in;
         const int64_t y0 = static_cast<int64_t>(t) * 32;
         if (y0 + 32 > n) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (y0 + 8 * (r >> 2) + 4 * comp + (r & 3) >= n) near &= ~(1u << (15 - r));
+            for (int v = 0; v < 16 * H; ++v)
+                if (y0 + 8 * ((v & 15) >> 2) + 4 * half + (v & 3) >= n)
+                    near &= ~(1u << (16 * H - 1 - v));
         }
         for (;;) {
             const uint64_t any = __ballot(near != 0u);
             if (!any) break;
             if (near) {
-                const int r = __builtin_clz(near) - 16;
-                near &= ~(0x8000u >> r);
-                const uint32_t y = static_cast<uint32_t>(y0) + 8 * (r >> 2) + 4 * comp + (r & 3);
-                me.q[qn + lanes_below(any)] = static_cast<uint32_t>(xl) | (y << 5);
+                const uint32_t v = static_cast<uint32_t>(__builtin_clz(near)) - (32 - 16 * H);
+                near &= ~(0x80000000u >> (v + 32 - 16 * H));
+                const uint32_t y = static_cast<uint32_t>(y0) + 8 * ((v & 15u) >> 2) +
+                                   4 * static_cast<uint32_t>(half) + (v & 3u);
+                me.q[qn + lanes_below(any)] = (static_cast<uint32_t>(xl) + 32 * (v >> 4)) | (y << 6);
             }
             qn += static_cast<uint32_t>(__popcll(any));
             if (qn >= 64) {
@@ -342,21 +360,29 @@ __global__ __launch_bounds__(kPairsThreads) void pairs_kernel(
     }
     if (qn) flush(qn);
     if (ln) flush_long(ln);
-    // the waves' sums in wave order (through the contribution arrays)
-    me.con[0][lane] = acc.hi;
-    me.con[1][lane] = acc.lo;
-    __syncthreads();
-    if (wave == 0) {
-        Acc2 s;
-        for (int w = 0; w < kPairsWaves; ++w) s.add(waves[w].con[0][lane], waves[w].con[1][lane]);
-        const int64_t i = x0 + xl;
-        if (i < n) {
-            if (gridDim.y == 1) {
-                sc.part[2 * i + comp] = s.value();
-            } else {
-                double *p = sc.part + 4 * (static_cast<int64_t>(blockIdx.y) * n + i) + 2 * comp;
-                p[0] = s.hi;
-                p[1] = s.lo;
+    // the waves' sums in wave order (through the contribution arrays), one
+    // component at a time
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        __syncthreads();
+        me.con[0][lane] = acc[h].hi;
+        me.con[1][lane] = acc[h].lo;
+        __syncthreads();
+        if (wave == h) {
+            Acc2 s;
+            for (int w = 0; w < kPairsWaves; ++w)
+                s.add(waves[w].con[0][lane], waves[w].con[1][lane]);
+            const int comp = H == 1 ? half : h;
+            const int64_t i = x0 + (H == 1 ? xl : lane);
+            if (i < n) {
+                if (gridDim.y == 1) {
+                    sc.part[2 * i + comp] = s.value();
+                } else {
+                    double *p =
+                        sc.part + 4 * (static_cast<int64_t>(blockIdx.y) * n + i) + 2 * comp;
+                    p[0] = s.hi;
+                    p[1] = s.lo;
+                }
             }
         }
     }
@@ -418,10 +444,19 @@ hipError_t launch_pairs(const DevTable &tab, const DevScratch &sc, const double 
                         uint32_t *sign_bits, int64_t sign_words, hipStream_t st) {
     const bool dump = hit_idx || sign_bits;
     const bool f32 = precision == NQS_FP32_KAHAN && !dump && !tab.sc;
-    const dim3 grid(static_cast<unsigned>((n + 31) / 32), static_cast<unsigned>(sc.pairs_split));
+    const bool wide = n > kPairsWide;
+    const int64_t rows = wide ? 64 : 32;
+    const dim3 grid(static_cast<unsigned>((n + rows - 1) / rows),
+                    static_cast<unsigned>(sc.pairs_split));
 #define NQS_AP(Wd, D, Pr, SCI)                                                                  \
-    hipLaunchKernelGGL((pairs_kernel<Wd, D, Pr, SCI>), grid, dim3(kPairsThreads), 0, st, tab, sc, \
-                       n, log_amp, phase, hit_idx, sign_bits, sign_words)
+    do {                                                                                        \
+        if (wide)                                                                               \
+            hipLaunchKernelGGL((pairs_kernel<Wd, 2, D, Pr, SCI>), grid, dim3(kPairsThreads), 0, \
+                               st, tab, sc, n, log_amp, phase, hit_idx, sign_bits, sign_words); \
+        else                                                                                    \
+            hipLaunchKernelGGL((pairs_kernel<Wd, 1, D, Pr, SCI>), grid, dim3(kPairsThreads), 0, \
+                               st, tab, sc, n, log_amp, phase, hit_idx, sign_bits, sign_words); \
+    } while (0)
     const bool w1 = tab.n_qubits <= 63;
     if (tab.sc) {
         if (w1) {
