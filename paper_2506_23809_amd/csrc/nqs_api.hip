@@ -652,7 +652,8 @@ int create_handle(nqs_ham *out, const nqs::HostTable &T, const std::vector<doubl
             index[s] = ~0ull;
             if (g == 0xFFFFFFFFu) continue;
             const uint64_t terms = std::min<int64_t>(T.goff[g + 1] - T.goff[g], 255);
-            index[s] = g | (terms << 32) | (static_cast<uint64_t>(T.ghm[2 * g] & 0xFFFFFFu) << 40);
+            const uint32_t hash = nqs::group_hash(T.gx[2 * g], T.gx[2 * g + 1]);
+            index[s] = g | (terms << 32) | (static_cast<uint64_t>(hash & 0xFFFFFFu) << 40);
         }
     }
     const std::vector<uint64_t> &gx = h1 ? T.gx : R.rec;

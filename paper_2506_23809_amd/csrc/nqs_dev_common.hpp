@@ -509,33 +509,53 @@ __device__ __forceinline__ void ratio_f32(double da, double dphi, float &rr, flo
     ri = mag * sn;
 }
 
-// Index of the group with flip mask X, or -1 (the group index is keyed by
-// h(X), which the caller has: h(x') ^ h(x)); *cnt receives its terms (255:
-// or more; the integral form has none).
+// Index of the group with flip mask X, or -1; *cnt receives its terms (255:
+// or more; the integral form has none).  A bucket of four slots is read at
+// once, and one with a free slot ends the search: one round trip for nearly
+// every lookup, where single slots took the longest chain of a wave's 64
+// lanes (five or six).
 template <int W, bool SCV>
-__device__ __forceinline__ int64_t group_find(const DevTable &tab, uint32_t hX, const Key<W> &X,
+__device__ __forceinline__ int64_t group_find(const DevTable &tab, const Key<W> &X,
                                               uint32_t *cnt) {
+    const uint32_t hX = group_hash(X.w[0], W == 2 ? X.w[W - 1] : 0ull);
     const uint32_t mask = 0xFFFFFFFFu >> tab.gh_shift;
-    uint32_t slot = slot_of(hX, tab.gh_shift);
-    for (uint32_t probe = 0; probe <= mask; ++probe) {
-        uint32_t g;
-        bool eq = true;
+    uint32_t slot = slot_of(hX, tab.gh_shift) & ~3u;
+    for (uint32_t probe = 0; probe <= mask; probe += 4) {
+        uint32_t g[4], info[4];
         if constexpr (SCV) {
-            g = static_cast<const uint32_t *>(tab.gh)[slot];
-            if (g == 0xFFFFFFFFu) return -1;
+            const uint4 a = *reinterpret_cast<const uint4 *>(
+                static_cast<const uint32_t *>(tab.gh) + slot);
+            g[0] = a.x; g[1] = a.y; g[2] = a.z; g[3] = a.w;
         } else {
-            const uint64_t v = static_cast<const uint64_t *>(tab.gh)[slot];
-            if (v == ~0ull) return -1;
-            g = static_cast<uint32_t>(v);
-            *cnt = static_cast<uint32_t>(v >> 32) & 0xFFu;
-            eq = (v >> 40) == (hX & 0xFFFFFFu);
+            const uint4 *p = reinterpret_cast<const uint4 *>(
+                static_cast<const uint64_t *>(tab.gh) + slot);
+            const uint4 a = p[0], b = p[1];
+            g[0] = a.x; g[1] = a.z; g[2] = b.x; g[3] = b.z;
+            info[0] = a.y; info[1] = a.w; info[2] = b.y; info[3] = b.w;
         }
-        if (eq) {
+        uint32_t match = 0;
 #pragma unroll
-            for (int q = 0; q < W; ++q) eq = eq && group_x<W>(tab, g, q) == X.w[q];
-            if (eq) return g;
+        for (int k = 0; k < 4; ++k) {
+            bool m = g[k] != 0xFFFFFFFFu;
+            if constexpr (!SCV) m = m && (info[k] >> 8) == (hX & 0xFFFFFFu);
+            match |= m ? 1u << k : 0u;
         }
-        slot = (slot + 1) & mask;
+        while (match) {
+            const int k = __builtin_ctz(match);
+            match &= match - 1;
+            const uint32_t gk = k == 0 ? g[0] : k == 1 ? g[1] : k == 2 ? g[2] : g[3];
+            bool eq = true;
+#pragma unroll
+            for (int q = 0; q < W; ++q) eq = eq && group_x<W>(tab, gk, q) == X.w[q];
+            if (eq) {
+                if constexpr (!SCV)
+                    *cnt = (k == 0 ? info[0] : k == 1 ? info[1] : k == 2 ? info[2] : info[3]) & 0xFFu;
+                return gk;
+            }
+        }
+        // (slots fill in order: a free one is the last)
+        if (g[3] == 0xFFFFFFFFu) return -1;
+        slot = (slot + 4) & mask;
     }
     return -1;
 }

@@ -481,7 +481,7 @@ __device__ __forceinline__ bool join_hit(const DevTable &tab, const Key<W> &x, c
     // spans several sectors also spin-changing ones), so the group index
     // decides in the integral form too
     uint32_t cnt = 0;
-    const int64_t g = group_find<W, SCV>(tab, linear_hash<W>(d, tab.hr), d, &cnt);
+    const int64_t g = group_find<W, SCV>(tab, d, &cnt);
     if constexpr (DUMP) {
         if (hit_idx && g >= 0) hit_idx[i * tab.n_groups + g] = j;
     }

@@ -579,7 +579,7 @@ __device__ __forceinline__ void enum_candidate(
     if (j < 0) return;
     int64_t g = -1;
     uint32_t terms = 0;
-    if (!SCV || DUMP) g = group_find<W, SCV>(tab, e.y ^ hx, X, &terms);
+    if (!SCV || DUMP) g = group_find<W, SCV>(tab, X, &terms);
     if constexpr (DUMP) {
         if (hit_idx && g >= 0) hit_idx[idx * tab.n_groups + g] = j;
     }

@@ -141,7 +141,6 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
     if (!pairs_chosen(sc)) return;
     constexpr int R = 32 * H;  // samples x of the block
     __shared__ PairRec xs[R];
-    __shared__ uint32_t hr[128];
     __shared__ PairsWave waves[kPairsWaves];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t x0 = static_cast<int64_t>(blockIdx.x) * R;
@@ -150,7 +149,6 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
         const int64_t i = x0 + threadIdx.x;
         xs[threadIdx.x] = i < n ? rec[i] : PairRec{0, 0, 0.0, 0.0};
     }
-    if (threadIdx.x < 128) hr[threadIdx.x] = tab.hr[threadIdx.x];
     __syncthreads();
     PairsWave &me = waves[wave];
     // the sums of x: with 32 samples lane comp 32 + xl has component comp of
@@ -252,7 +250,7 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
                         if constexpr (W == 2) pa += __popcll(d.w[W - 1] & tab.spin_a1);
                         g = (pop == 2 || pop == 4) && (pa & 1) == 0 ? 0 : -1;
                     } else {
-                        g = group_find<W, SCV>(tab, linear_hash<W>(d, hr), d, &cnt);
+                        g = group_find<W, SCV>(tab, d, &cnt);
                     }
                     if constexpr (DUMP) {
                         if (hit_idx && g >= 0)

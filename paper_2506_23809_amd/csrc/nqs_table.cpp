@@ -273,7 +273,8 @@ void build_enum_index(HostTable *T) {
     const uint32_t mask = static_cast<uint32_t>(cap - 1);
     for (int64_t g = 0; g < T->n_groups; ++g) {
         T->max_flip = std::max(T->max_flip, popc2(T->gx[2 * g], T->gx[2 * g + 1]));
-        uint32_t slot = (T->ghm[2 * g] * 0x9E3779B1u) >> T->gh_shift;
+        uint32_t slot =
+            ((group_hash(T->gx[2 * g], T->gx[2 * g + 1]) * 0x9E3779B1u) >> T->gh_shift) & ~3u;
         while (T->gh[slot] != 0xFFFFFFFFu) slot = (slot + 1) & mask;
         T->gh[slot] = static_cast<uint32_t>(g);
     }

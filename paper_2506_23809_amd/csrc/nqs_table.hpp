@@ -24,6 +24,16 @@ struct LinearHash {
     uint32_t operator()(uint64_t w0, uint64_t w1) const;
 };
 
+// Hash of a flip mask in the group index.
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline uint32_t group_hash(uint64_t w0, uint64_t w1) {
+    uint64_t s = (w0 & 0xFFFFFFFFull) * 0x9E3779B1u + (w0 >> 32) * 0x85EBCA77u;
+    s += (w1 & 0xFFFFFFFFull) * 0xC2B2AE3Du + (w1 >> 32) * 0x27D4EB2Fu;
+    return static_cast<uint32_t>(s) ^ static_cast<uint32_t>(s >> 32);
+}
+
 struct HostTable {
     int n_qubits = 0;
     int words = 1;                 // 1 when n_qubits <= 63, else 2
@@ -55,7 +65,8 @@ struct HostTable {
     // the class of a bit string, the XOR over its set qubits, picks the
     // filter partition of a sample; alpha flips leave it unchanged
     uint8_t qcls[128] = {};
-    // group index by X: open addressing on (h(X) * golden) >> gh_shift,
+    // group index by X: open addressing from the bucket of four slots that
+    // holds (group_hash(X) * golden) >> gh_shift,
     // linear probing, 0xFFFFFFFF = empty; keys are compared through gx
     std::vector<uint32_t> gh;
     uint32_t gh_shift = 0;
