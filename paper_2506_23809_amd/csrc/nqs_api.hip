@@ -151,9 +151,10 @@ nqs::DevScratch scratch_of(nqs_ham h) {
 // The comparison of all pairs, its scratch in the space of the sample hash
 // (kMinSlots or 4 n slots hold it: 32 or 64 bytes of operand and a 32-byte
 // record per sample, against 64 or 96 bytes of slots).
-void set_pairs(nqs::DevScratch *s, nqs_ham h, const nqs::EvalLaunch &L, char *slots) {
+void set_pairs(nqs::DevScratch *s, nqs_ham h, const nqs::EvalLaunch &L, char *slots, void *join) {
     s->pairs = L.pairs;
     s->pairs_split = L.pairs_split;
+    s->ppart = L.pairs_in_join ? static_cast<double *>(join) : s->part;
     if (L.pairs) nqs::pairs_scratch_layout(h->dt, L.n, slots, s);
 }
 
@@ -167,13 +168,16 @@ void set_filters(nqs::DevScratch *s, nqs_ham h, const nqs::EvalLaunch &L) {
         nqs::join_scratch_layout(h->dt, L.n, L.join_log2m, static_cast<char *>(h->jmem), s);
         s->join_force = L.join_force;
     }
-    set_pairs(s, h, L, static_cast<char *>(h->slots));
+    set_pairs(s, h, L, static_cast<char *>(h->slots), h->jmem);
 }
 
 // Partial-sum slots per sample a plan needs: its group chunks, or one per
 // join block when the pair join may run.
 int64_t plan_chunks(const nqs_ham h, const nqs::EvalLaunch &L) {
-    const int64_t c = L.n_chunks > 0 ? L.n_chunks : 1;
+    int64_t c = L.n_chunks > 0 ? L.n_chunks : 1;
+    // (a divided comparison of all pairs keeps double-doubles)
+    if (L.pairs && L.pairs_split > 1 && !L.pairs_in_join)
+        c = std::max<int64_t>(c, 2 * L.pairs_split);
     return L.join_scratch ? std::max<int64_t>(c, h->dt.join_blocks) : c;
 }
 
@@ -323,7 +327,7 @@ struct EvalKey {
     const void *slots, *shx, *part, *filter, *efilter, *small, *eblk, *jmem;
     uint32_t slot_cap;
     int energy, join_only;
-    int pairs, pairs_split;
+    int pairs, pairs_split, pairs_in_join;
     const void *epart, *ehost;
 };
 static_assert(sizeof(EvalKey) <= sizeof(nqs_ham_s::eval_key), "key fits");
@@ -465,6 +469,7 @@ int eval_impl(nqs_ham h, int64_t n, const uint64_t *samples, const int64_t *weig
         key.join_only = L.join_only;
         key.pairs = L.pairs;
         key.pairs_split = L.pairs_split;
+        key.pairs_in_join = L.pairs_in_join;
         key.epart = energy ? h->epart : nullptr;
         key.ehost = energy ? h->ehost : nullptr;
         const bool same = h->have_key && std::memcmp(h->eval_key, &key, sizeof key) == 0;
@@ -577,7 +582,7 @@ size_t layout_scratch(nqs_ham h, const nqs::EvalLaunch &L, int64_t n, int n_cu, 
         nqs::join_scratch_layout(h->dt, n, L.join_log2m, base + off[6], sc);
         sc->join_force = L.join_force;
     }
-    set_pairs(sc, h, L, base + off[0]);
+    set_pairs(sc, h, L, base + off[0], base + off[6]);
     return total;
 }
 
@@ -1566,6 +1571,8 @@ int plan_batch(const nqs_batch_item *items, int n_items, int threads, hipStream_
             L.n_chunks = 1;
             L.chunk_len = h->dt.n_groups - L.g_first;
         }
+        // (the batch's partials have no more room than the join's)
+        if (!L.pairs_in_join && L.pairs_split > 2 && L.join_scratch) L.pairs_split = 2;
         int rc = ensure_scratch(h, std::max<int64_t>(it.n, 1), plan_chunks(h, L), st,
                                 L.eparts_log2 > 0, plan_join_bytes(h, L));
         if (!rc) rc = scratch_ready(h, L);

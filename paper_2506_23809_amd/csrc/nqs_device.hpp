@@ -234,10 +234,11 @@ struct DevScratch {
     int join_force;             // 1: join whenever it can run, 0: when cheaper
     // comparison of all pairs: 0 none, 1 for this launch, 2 unless the device
     // chose the pair join; its operands and records (in the space of the
-    // sample hash, which such a launch does not build), and the shares the
-    // samples y are split into (one partial each)
+    // sample hash, which such a launch does not build), the shares the
+    // samples y are split into (one partial each) and those partials
     int pairs;
     int pairs_split;
+    double *ppart;              // [pairs_split][n][2] double-doubles (re, im); undivided [n][2]
     char *pops;
     char *prec;
 };
@@ -308,8 +309,10 @@ struct EvalLaunch {
     // streaming (DevScratch::pairs), and the shares of its columns
     int pairs;
     int pairs_split;
+    int pairs_in_join;  // 1: its partials in the pair join's scratch
     // 1: the scratch holds the pair join's arrays (also where all pairs are
-    // compared without it: the space a handle takes follows from n alone)
+    // compared without it, which then keeps its partials there: the space a
+    // handle takes follows from n alone)
     int join_scratch;
 };
 

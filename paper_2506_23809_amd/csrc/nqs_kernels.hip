@@ -1905,7 +1905,7 @@ __device__ __forceinline__ void finish_one(const DevTable &tab, const DevScratch
             Acc2 r, m;
             for (int s = 0; s < sc.pairs_split; ++s) {
                 const double2 *p = reinterpret_cast<const double2 *>(
-                    sc.part + 4 * (static_cast<int64_t>(s) * n + i));
+                    sc.ppart + 4 * (static_cast<int64_t>(s) * n + i));
                 const double2 a = p[0], b = p[1];
                 r.add(a.x, a.y);
                 m.add(b.x, b.y);
@@ -2666,15 +2666,36 @@ EvalLaunch plan_eval(const DevTable &tab, int64_t n, bool dump, const Tuning *tu
     L.join_scratch = L.join;
     L.pairs = 0;
     L.pairs_split = 1;
+    L.pairs_in_join = 0;
     if (want == kStrategyAuto && pairs_cheaper(tab, n)) {
         L.pairs = L.join && n > kPairsDirect ? 2 : 1;
         if (L.pairs == 1) L.join = 0;
-        // two shares of the columns, for more and shorter blocks (a share's
-        // partial takes the room of two): 20,001 gathered samples at 100
-        // qubits 508 us with one, 411 with two
-        const int64_t room = L.join_scratch ? tab.join_blocks : 0;
-        if ((L.n_chunks > room ? L.n_chunks : room) >= 4)
-            L.pairs_split = 2;
+        // two shares of the columns, for shorter blocks, and up to four
+        // until every compute unit has two (a share's partial takes the room
+        // of two; the join's scratch is free where no join is launched):
+        // 20,001 gathered samples at 100 qubits 508 us with one, 411 with
+        // two; at 40 qubits 4,096 take 37.3 with two, 31.9 with four and 38.8
+        // with eight, 8,192 74.7, 78.0 and 87.8; 400 at 12 qubits 21.8 and
+        // 16.0
+        const int64_t chunks = L.join_scratch && L.n_chunks < tab.join_blocks
+                                   ? tab.join_blocks : L.n_chunks;
+        int64_t room = chunks / 2;
+        if (L.pairs == 1 && L.join_scratch) {
+            const size_t in_join = join_scratch_bytes(tab, n, L.join_log2m) / (32 * n);
+            if (static_cast<int64_t>(in_join) > room) {
+                room = static_cast<int64_t>(in_join);
+                L.pairs_in_join = 1;
+            }
+        }
+        const int64_t rows = (n + 31) / 32;
+        int64_t want_split = 2 * device_cus() / rows;
+        if (want_split < 2) want_split = 2;
+        if (want_split > 4) want_split = 4;
+        L.pairs_split = static_cast<int>(want_split < room ? want_split : room);
+        if (L.pairs_split < 2) {
+            L.pairs_split = 1;
+            L.pairs_in_join = 0;
+        }
     }
     return L;
 }

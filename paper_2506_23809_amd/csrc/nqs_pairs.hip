@@ -268,7 +268,8 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
         const uint64_t lm = __ballot(later);
         if (later) me.lq[ln + lanes_below(lm)] = make_uint2(e, static_cast<uint32_t>(g));
         ln += static_cast<uint32_t>(__popcll(lm));
-        deposit(now, x, re, im);
+        // (near pairs need not be connected)
+        if (__ballot(now)) deposit(now, x, re, im);
         if (ln >= 64) {
             flush_long(64);
             ln -= 64;
@@ -296,9 +297,19 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
     v16f cthr;
 #pragma unroll
     for (int r = 0; r < 16; ++r) cthr[r] = thr;
-    // this wave's tiles: every step-th
-    const int step = kPairsWaves * static_cast<int>(gridDim.y);
+    // this wave's tiles: every step-th; with more waves than tiles several
+    // share a tile, each taking every share-th of its values
+    const int all = kPairsWaves * static_cast<int>(gridDim.y);
+    const int share = all >= 2 * tiles ? (all >= 8 * tiles ? 8 : (all >= 4 * tiles ? 4 : 2)) : 1;
+    const int step = all / share;
     int t = wave + kPairsWaves * static_cast<int>(blockIdx.y);
+    // (values v = t / step modulo share)
+    uint32_t mine = x_in;
+    if (share > 1) {
+        const uint32_t every = share == 2 ? 0x55555555u : (share == 4 ? 0x11111111u : 0x01010101u);
+        mine &= every << (t / step);
+        t %= step;
+    }
     v8i next[W];
 #pragma unroll
     for (int kb = 0; kb < W; ++kb) next[kb] = operand(t < tiles ? t : tiles - 1, kb);
@@ -328,7 +339,7 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
 #pragma unroll
         for (int v = 0; v < 16 * H; ++v)
             neg = (neg << 1) | (__float_as_uint(c[v >> 4][v & 15]) >> 31);
-        uint32_t near = ~neg & x_in;
+        uint32_t near = ~neg & mine;
         const int64_t y0 = static_cast<int64_t>(t) * 32;
         if (y0 + 32 > n) {
 #pragma unroll
@@ -374,10 +385,10 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
             const int64_t i = x0 + (H == 1 ? xl : lane);
             if (i < n) {
                 if (gridDim.y == 1) {
-                    sc.part[2 * i + comp] = s.value();
+                    sc.ppart[2 * i + comp] = s.value();
                 } else {
                     double *p =
-                        sc.part + 4 * (static_cast<int64_t>(blockIdx.y) * n + i) + 2 * comp;
+                        sc.ppart + 4 * (static_cast<int64_t>(blockIdx.y) * n + i) + 2 * comp;
                     p[0] = s.hi;
                     p[1] = s.lo;
                 }
