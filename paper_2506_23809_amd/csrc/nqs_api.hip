@@ -685,7 +685,7 @@ int create_handle(nqs_ham *out, const nqs::HostTable &T, const std::vector<doubl
         {gx.data(), sizeof(uint64_t) * gx.size(), 0},
         {T.gsec.data(), sizeof(uint64_t) * T.gsec.size(), 0},
         {T.ghm.data(), sizeof(uint32_t) * T.ghm.size(), 0},
-        {goff32.data(), sizeof(uint32_t) * goff32.size(), 0},
+        {goff32.data(), h1 ? 0 : sizeof(uint32_t) * goff32.size(), 0},
         {R.z.data(), sizeof(uint64_t) * R.z.size(), 0},
         {T.tc.data(), sizeof(double) * T.tc.size(), 0},
         {R.codes.data(), R.codes.size(), 0},
@@ -748,7 +748,7 @@ int create_handle(nqs_ham *out, const nqs::HostTable &T, const std::vector<doubl
     d.gx_stride = h1 ? 2 : nqs::kGroupWords;
     d.gsec = reinterpret_cast<const uint64_t *>(base + pieces[1].off);
     d.ghm = reinterpret_cast<const uint32_t *>(base + pieces[2].off);
-    d.goff = reinterpret_cast<const uint32_t *>(base + pieces[3].off);
+    d.goff = h1 ? nullptr : reinterpret_cast<const uint32_t *>(base + pieces[3].off);
     d.tz = reinterpret_cast<const uint64_t *>(base + pieces[4].off);
     d.tc = reinterpret_cast<const double *>(base + pieces[5].off);
     d.tcode = reinterpret_cast<const uint8_t *>(base + pieces[6].off);
@@ -873,6 +873,20 @@ int nqs_ham_create_integrals(nqs_ham *out, int n_orbitals, const double *h1e, co
         std::string err;
         const int rc = nqs::build_flip_table(K, &T, &err);
         if (rc) return fail(rc, err);
+        // the diagonal in occupation form: h_ii per spin orbital, and per pair
+        // of them the Coulomb integral, less the exchange one for equal spins
+        const int nq = 2 * K;
+        T.diag.assign(1 + nq + size_t(nq) * (nq - 1) / 2, 0.0);
+        for (int j = 0; j < nq; ++j) {
+            const int b = j >> 1;
+            T.diag[1 + j] = h1[size_t(b) * K + b];
+            for (int i = 0; i < j; ++i) {
+                const int a = i >> 1;
+                T.diag[1 + nq + size_t(j) * (j - 1) / 2 + i] =
+                    E(a, a, b, b) - ((i & 1) == (j & 1) ? E(a, b, b, a) : 0.0);
+            }
+        }
+        T.diag_occ = true;
         return create_handle(out, T, &h1, &packed, K, static_cast<hipStream_t>(hip_stream));
     } catch (const std::bad_alloc &) {
         return fail(NQS_E_NOMEM, "host allocation failed");

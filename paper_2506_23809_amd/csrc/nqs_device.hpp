@@ -29,7 +29,7 @@ struct DevTable {
     int gx_stride;
     const uint64_t *gsec;  // [G][2] flip mask compressed to (alpha bits, beta bits)
     const uint32_t *ghm;   // [G][2] (linear hash of X, sector key)
-    const uint32_t *goff;  // [G + 1] term offsets
+    const uint32_t *goff;  // [G + 1] term offsets (null in the integral form)
     const uint64_t *tz;    // [..][2] Z masks of the general groups' terms (group 0 first)
     const uint8_t *tcode;  // [T] flips in the Z mask of a tabulated group's term
     const double *tc;      // [T] folded coefficients

@@ -1952,7 +1952,7 @@ __device__ __forceinline__ void finish_one(const DevTable &tab, const DevScratch
     }
     // every sample sums the whole X = 0 group: one count for the batch
     (void)n_terms;
-    if (!SCV && tab.has_diagonal && blockIdx.x == 0 && threadIdx.x == 0)
+    if (!SCV && !tab.sc && tab.has_diagonal && blockIdx.x == 0 && threadIdx.x == 0)
         count_add(sc.counters, 3,
                   static_cast<unsigned long long>(n) * (tab.goff[1] - tab.goff[0]));
 }
@@ -2100,7 +2100,7 @@ __global__ __launch_bounds__(256) void eloc_finish_kernel(
 }
 
 // The finish kernel of tables with the occupation-form diagonal (no debug
-// dump, Pauli form): the digit tiles staged in LDS once per block, the
+// dump): the digit tiles staged in LDS once per block, the
 // diagonal of each wave's 64 samples on the matrix cores, then the partials.
 constexpr int kFinishMfmaThreads = 1024;
 constexpr int kDiagMaxTiles = diag_mfma_tiles(8);
@@ -2290,17 +2290,7 @@ __global__ __launch_bounds__(256) void batch_finish_kernel(const JobDesc *__rest
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (static_cast<int64_t>(blockIdx.x) * blockDim.x >= J.n) return;  // whole block past the end
     const int64_t chunks = J.chunk_len > 0 ? J.n_chunks : 0;
-    const bool integrals = (J.kind & kJobIntegrals) != 0;
     const bool en = J.strategy == kStrategyEnum;
-    if (integrals) {
-        if ((J.kind & 1) == 0)
-            finish_one<1, false, NQS_FP64, true>(J.tab, J.sc, J.samples, J.n, chunks, en, J.eloc,
-                                                 nullptr, nullptr, 0, i);
-        else
-            finish_one<2, false, NQS_FP64, true>(J.tab, J.sc, J.samples, J.n, chunks, en, J.eloc,
-                                                 nullptr, nullptr, 0, i);
-        return;
-    }
     // the same diagonal evaluation as the single-launch finish kernels
     if (J.tab.diag_jtiles > 0) {
         const diag_v4i *tiles = reinterpret_cast<const diag_v4i *>(J.tab.diag_q8);
@@ -2930,8 +2920,10 @@ hipError_t launch_eloc(const DevTable &tab, const DevScratch &sc, const EvalLaun
     const size_t stage_bytes =
         (dump || tab.sc) ? 0
                          : sizeof(double) * stage_cap + (f32 ? size_t(256) * 4 * list_words : 0);
-    if (!dump && !tab.sc && tab.diag_jtiles > 0) {
-        // the occupation-form diagonal on the matrix cores
+    if (!dump && tab.diag_jtiles > 0) {
+        // the occupation-form diagonal on the matrix cores (the integral form
+        // has it too: its sum over occupied pairs took 53 us of 8,193 samples
+        // at 40 qubits)
         // 1024-thread blocks once they fill every CU (each block stages the
         // digit tiles once), else 256-thread blocks to spread a small batch
         const int mth = n >= 256 * int64_t(kFinishMfmaThreads) ? kFinishMfmaThreads : 256;
@@ -2973,11 +2965,8 @@ hipError_t launch_eloc(const DevTable &tab, const DevScratch &sc, const EvalLaun
                        sc, samples, n, chunks, fb, eloc, hit_idx, sign_bits, sign_words, 0, 0,    \
                        ef.weights, ep)
     if (tab.sc) {
-        if (words == 1) {
-            if (dump) NQS_FINISH_SC(1, true); else NQS_FINISH_SC(1, false);
-        } else {
-            if (dump) NQS_FINISH_SC(2, true); else NQS_FINISH_SC(2, false);
-        }
+        // (a dump: others took the matrix-core form above)
+        if (words == 1) NQS_FINISH_SC(1, true); else NQS_FINISH_SC(2, true);
     } else if (words == 1) {
         if (dump) NQS_FINISH(1, true, NQS_FP64);
         else if (f32) NQS_FINISH(1, false, NQS_FP32_KAHAN);
