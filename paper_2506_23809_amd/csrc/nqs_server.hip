@@ -139,6 +139,7 @@ void retire_lane(nqs_server s, Lane &l, const Clock::time_point now, bool ok) {
 void dispatcher(nqs_server s) {
     (void)hipSetDevice(s->device);
     std::unique_lock<std::mutex> lk(s->mu);
+    Clock::time_point progress = Clock::now();  // last admission or completion
     for (;;) {
         // 1. retire finished requests
         const Clock::time_point now = Clock::now();
@@ -197,12 +198,24 @@ void dispatcher(nqs_server s) {
             }
             launched = true;
         }
-        if (launched) continue;
-        // 3. wait: poll completions while requests run, sleep when idle
-        if (any_busy)
+        if (launched || retired) {
+            progress = Clock::now();
+            continue;
+        }
+        // 3. wait: while requests run, poll their completion (a sleep of 20 us
+        // ends 50 us or more late, longer than most requests take: 24 of them
+        // on four lanes took 774 us), with sleeps only once nothing has moved
+        // for a while; sleep when idle
+        if (any_busy && Clock::now() - progress < std::chrono::milliseconds(1)) {
+            lk.unlock();
+            std::this_thread::yield();
+            lk.lock();
+        } else if (any_busy) {
             s->cv.wait_for(lk, std::chrono::microseconds(20));
-        else
+        } else {
             s->cv.wait(lk, [s] { return s->stop || (!s->pending.empty() && !s->error); });
+            progress = Clock::now();
+        }
     }
 }
 
