@@ -21,7 +21,8 @@
 // partition is sorted in LDS by (bucket, content fingerprint), and
 // the start and size of each entry's group (its bucket's members with its
 // fingerprint: hash-colliding contents mostly fall apart) are written beside
-// the entries.  The pair kernel then takes one lane per entry.
+// the entries.  The pair kernel then takes one lane per
+// entry, or compares large groups as matrix tiles.
 //
 // Cost: the ordered pairs inside groups, the sum of squared group sizes.
 // For samples spread over a large sector this is far below the
@@ -49,9 +50,16 @@ namespace nqs {
 
 namespace {
 
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
 constexpr int kJoinGroupThreads = 1024;  // tile kernels
 constexpr int kJoinPairThreads = 256;
 constexpr int kJoinPairPer = 4;  // entries per lane of the pair kernel, at most
+// Samples per content of the shortest block from which groups are compared
+// as matrix tiles (spread samples, one lane an entry and tiles: 8.9 and 6.6 us
+// at 8, 5.7 and 6.4 at 6).
+constexpr int64_t kJoinTileGroup = 8;
 constexpr int kJoinSortThreads = 512;
 // Largest bucket split by a pass over its members; a larger one stays whole.
 constexpr uint32_t kJoinRankMax = 64;
@@ -364,7 +372,7 @@ __device__ __forceinline__ void join_sort_partition(const DevTable &tab, const D
 // (by one whole block).
 __device__ __forceinline__ void join_decide(const DevTable &tab, const DevScratch &sc,
                                             const uint64_t *__restrict__ samples, int64_t n,
-                                            int64_t g_eff) {
+                                            int64_t g_eff, bool tiles) {
     unsigned long long q = 0, m = 0;
     for (int p = threadIdx.x; p < sc.join_parts; p += blockDim.x) {
         q += sc.jstat[2 * p];
@@ -388,7 +396,9 @@ __device__ __forceinline__ void join_decide(const DevTable &tab, const DevScratc
     sc.jctl[kJoinCtlProbes] = probes;
     // costs in units of one enumeration probe (0.47 ps), from MI355X timings of both
     // strategies over 64 molecule-shaped jobs (24..100 qubits, 10^3..2.6 10^5
-    // samples): a candidate pair of the join costs about 4 probes, an entry
+    // samples): a candidate pair of the join costs about 4 probes (as matrix
+    // tiles 0.2, counted as one for the near pairs that come up in several
+    // blocks), an entry
     // (its grouping and its share of the pair kernel) about 40, the join's
     // extra launches about 10^7; a probe against a filter split into class
     // partitions costs about 4 (each round walks the partitions).  Hits cost
@@ -398,24 +408,29 @@ __device__ __forceinline__ void join_decide(const DevTable &tab, const DevScratc
                            : 0.5 * static_cast<double>(n) * static_cast<double>(g_eff);
     const double entries = static_cast<double>(tab.join_blocks) * static_cast<double>(n);
     const double cand = static_cast<double>(q) > entries ? static_cast<double>(q) - entries : 0.0;
-    const double cost = 4.0 * cand + 40.0 * entries + 1.0e7;
+    const double cost = (tiles ? 1.0 : 4.0) * cand + 40.0 * entries + 1.0e7;
     const bool fits = sc.jctl[kJoinCtlOver] == 0ull;
     bool chosen = fits && (sc.join_force != 0 || cost < alt);
     if (sc.pairs == 2) {
         // beside the comparison of all pairs (0.09 ps a pair, 0.055 in wide
         // blocks, and 8 us) the
         // grouping is spent either way: what counts is the pair kernel, about
-        // two probes a candidate and 18 an entry (79 us for 86.9 M candidates
-        // at 40 qubits, 11 us for 1.3 M entries at 100), and the serial chain
-        // of its largest group, 0.1 us a member of one word and 0.7 us of
-        // two.  A call's time with the join and with all pairs: 72 and 75 us
-        // (40 qubits, 9,000 spread samples), 121 and 200 (37,843), 468 and
-        // 203 (37,843 somewhat gathered ones, 2,127 in a group), 280 and 150
-        // (100 qubits, 20,001, 307 in a group)
+        // two probes a candidate and 18 an entry (11 us for 1.3 M entries at
+        // 100 qubits), and the serial chain of its largest group, 0.1 us a
+        // member of one word and 0.7 us of two.  As matrix tiles a candidate
+        // costs 0.2 probes and an entry 30 (40 qubits, 262,144 spread samples:
+        // 128 us for 1.39 G candidates); a whole probe is counted for the
+        // near pairs, which come up in every block on which they agree, and
+        // 0.01 us a member of the largest group.  A call's time with the
+        // tiles and with all pairs: 53 and 72 us (40 qubits, 9,000 spread
+        // samples), 114 and 136 (37,843 a little gathered ones), 161 and 265
+        // (65,536), 315 and 88 (9,000 gathered ones)
         const double dn = static_cast<double>(n);
-        const double chain = (tab.n_qubits <= 63 ? 2.1e5 : 1.5e6) * static_cast<double>(m);
-        chosen = fits && 2.0 * cand + 18.0 * entries + chain <
-                             (n > kPairsWide ? 0.117 : 0.19) * dn * dn + 1.7e7;
+        const double md = static_cast<double>(m);
+        const double pair_cost =
+            tiles ? cand + 30.0 * entries + 2.0e4 * md
+                  : 2.0 * cand + 18.0 * entries + (tab.n_qubits <= 63 ? 2.1e5 : 1.5e6) * md;
+        chosen = fits && pair_cost < (n > kPairsWide ? 0.117 : 0.19) * dn * dn + 1.7e7;
     }
     sc.jctl[kJoinCtlCost] = q;
     sc.jctl[kJoinCtlMax] = m;
@@ -463,8 +478,9 @@ __global__ __launch_bounds__(kJoinSortThreads) void join_sort_kernel(
 // every block, which writes back the L2 of each XCD: far slower than a
 // launch.)
 __global__ __launch_bounds__(kJoinGroupThreads) void join_decide_kernel(
-    DevTable tab, DevScratch sc, const uint64_t *__restrict__ samples, int64_t n, int64_t g_eff) {
-    join_decide(tab, sc, samples, n, g_eff);
+    DevTable tab, DevScratch sc, const uint64_t *__restrict__ samples, int64_t n, int64_t g_eff,
+    bool tiles) {
+    join_decide(tab, sc, samples, n, g_eff, tiles);
 }
 
 // The contribution of partner j (bit string y = x ^ d) to E_loc(x), or no
@@ -476,7 +492,7 @@ __device__ __forceinline__ bool join_hit(const DevTable &tab, const Key<W> &x, c
                                          const double *__restrict__ phase,
                                          int32_t *__restrict__ hit_idx,
                                          uint32_t *__restrict__ sign_bits, int64_t sign_words,
-                                         unsigned long long *terms, Acc2 &re, Acc2 &im) {
+                                         unsigned long long *terms, double &re, double &im) {
     // any pair within the distance bound is a candidate (in a batch that
     // spans several sectors also spin-changing ones), so the group index
     // decides in the integral form too
@@ -496,17 +512,58 @@ __device__ __forceinline__ bool join_hit(const DevTable &tab, const Key<W> &x, c
             hsum = group_sum<W, DUMP>(tab, g, x, row, terms, cnt);
         }
         const double2 rat = amp_ratio_f64(log_amp[j] - la, phase[j] - ph);
-        re.add(hsum * rat.x);
-        im.add(hsum * rat.y);
+        re = hsum * rat.x;
+        im = hsum * rat.y;
     } else {
         const AccF32 hs = group_sum_f32<W>(tab, g, x, terms, cnt);
         float rr, ri;
         ratio_f32(log_amp[j] - la, phase[j] - ph, rr, ri);
         const float pre = hs.s * rr, pim = hs.s * ri;
-        re.add(static_cast<double>(pre) + static_cast<double>(fmaf(hs.s, rr, -pre) + hs.c * rr));
-        im.add(static_cast<double>(pim) + static_cast<double>(fmaf(hs.s, ri, -pim) + hs.c * ri));
+        re = static_cast<double>(pre) + static_cast<double>(fmaf(hs.s, rr, -pre) + hs.c * rr);
+        im = static_cast<double>(pim) + static_cast<double>(fmaf(hs.s, ri, -pim) + hs.c * ri);
     }
     return true;
+}
+
+// The first block on which two samples agree, d = x ^ y (join_blocks: none).
+template <int W>
+__device__ __forceinline__ int first_agreeing(const DevTable &tab, const Key<W> &d) {
+    int first = tab.join_blocks;
+#pragma unroll
+    for (int cb = kJoinMaxBlocks - 1; cb >= 0; --cb) {
+        if (cb < tab.join_blocks) {
+            uint64_t v = d.w[0] & tab.jmask[cb][0];
+            if constexpr (W == 2) v |= d.w[W - 1] & tab.jmask[cb][1];
+            if (v == 0ull) first = cb;
+        }
+    }
+    return first;
+}
+
+// One set of counter atomics per block of kJoinPairThreads.
+__device__ __forceinline__ void pair_counters(const DevScratch &sc, unsigned long long n_cand,
+                                              unsigned long long n_probe,
+                                              unsigned long long n_hit,
+                                              unsigned long long n_term) {
+    __shared__ unsigned long long cnt[4][kJoinPairThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    n_cand = wave_sum(n_cand);
+    n_probe = wave_sum(n_probe);
+    n_hit = wave_sum(n_hit);
+    n_term = wave_sum(n_term);
+    if (lane == 0) {
+        cnt[0][wave] = n_cand;
+        cnt[1][wave] = n_probe;
+        cnt[2][wave] = n_hit;
+        cnt[3][wave] = n_term;
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        unsigned long long v = 0;
+        for (int w = 0; w < kJoinPairThreads / 64; ++w) v += cnt[threadIdx.x][w];
+        const int slot[4] = {4, 1, 2, 3};
+        if (v) count_add(sc.counters, slot[threadIdx.x], v);
+    }
 }
 
 // One lane per entry with partners (block b, sample i; each wave gathers
@@ -576,16 +633,7 @@ __global__ __launch_bounds__(kJoinPairThreads) void join_pair_kernel(
                 }
                 if (pop > maxf) return;
                 // the first block on which x and y agree must be this one
-                int first = tab.join_blocks;
-#pragma unroll
-                for (int cb = kJoinMaxBlocks - 1; cb >= 0; --cb) {
-                    if (cb < tab.join_blocks) {
-                        uint64_t v = d.w[0] & tab.jmask[cb][0];
-                        if constexpr (W == 2) v |= d.w[W - 1] & tab.jmask[cb][1];
-                        if (v == 0ull) first = cb;
-                    }
-                }
-                if (first != b) return;
+                if (first_agreeing<W>(tab, d) != b) return;
                 if (pop == 0) {
                     latch(sc.err, NQS_E_DUPLICATE);
                     return;
@@ -597,9 +645,13 @@ __global__ __launch_bounds__(kJoinPairThreads) void join_pair_kernel(
                     ph = phase[i];
                     have_psi = true;
                 }
+                double cre, cim;
                 if (join_hit<W, DUMP, P, SCV>(tab, x, y, d, i, j, la, ph, log_amp, phase, hit_idx,
-                                              sign_bits, sign_words, &n_term, re, im))
+                                              sign_bits, sign_words, &n_term, cre, cim)) {
+                    re.add(cre);
+                    im.add(cim);
                     ++n_hit;
+                }
             };
             // one-word bit strings four at a time
             // (large buckets wait on these loads; two-word strings would
@@ -625,25 +677,217 @@ __global__ __launch_bounds__(kJoinPairThreads) void join_pair_kernel(
             }
         }
     }
-    // one set of counter atomics per block
-    __shared__ unsigned long long cnt[4][kJoinPairThreads / 64];
-    n_cand = wave_sum(n_cand);
-    n_probe = wave_sum(n_probe);
-    n_hit = wave_sum(n_hit);
-    n_term = wave_sum(n_term);
-    if (lane == 0) {
-        cnt[0][wave] = n_cand;
-        cnt[1][wave] = n_probe;
-        cnt[2][wave] = n_hit;
-        cnt[3][wave] = n_term;
+    pair_counters(sc, n_cand, n_probe, n_hit, n_term);
+}
+
+// Shared state of one wave of the tile kernel: its 64 rows (entries) and
+// the queue of near pairs.
+struct TileWave {
+    uint64_t key[64];
+    double con[2][64];           // contributions of a batch (re, im)
+    unsigned long long own[64];  // which of them belong to each row
+    uint2 range[64];             // the row's group: first entry, size
+    uint32_t who[64];            // the row's sample
+    uint32_t q[128];             // row | column entry << 6
+};
+
+// The pairs of large groups (one-word bit strings): each wave takes 64
+// consecutive entries and compares them with all entries of their groups
+// (which lie beside each other: one range of columns) as FP4 matrix
+// products of +-1, 64 x 32 pairs a step.  x . y = 64 - 2 distance(x, y) in any
+// order of the 64 bits, so the operands are made from the bit strings by a
+// shift and a mask per eight qubits.  Near pairs are queued and taken 64 at
+// a time; group, first agreeing block and the hit as in the pair kernel,
+// which a pair of two neighbouring groups does not pass.
+//
+// Bound: the latency of a step (two FP4 MFMAs, their 32 results, one load),
+// 0.09 ps a candidate.  40 qubits, spread samples, one lane an entry and
+// tiles: 9,000 12.8 and 7.3 us, 65,536 (86.8 M candidates) 85.3 and 20.6,
+// 262,144 773 and 128.
+template <int P, bool SCV>
+__global__ __launch_bounds__(kJoinPairThreads, 4) void join_tile_kernel(
+    DevTable tab, DevScratch sc, const uint64_t *__restrict__ samples,
+    const int64_t *__restrict__ weights, const double *__restrict__ log_amp,
+    const double *__restrict__ phase, int64_t n, unsigned build_blocks) {
+    if (blockIdx.x < build_blocks) {
+        const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+        if (i < n) hash_build_one<1>(tab, sc, samples, weights, i);
+        return;
     }
-    __syncthreads();
-    if (threadIdx.x < 4) {
-        unsigned long long v = 0;
-        for (int w = 0; w < kJoinPairThreads / 64; ++w) v += cnt[threadIdx.x][w];
-        const int slot[4] = {4, 1, 2, 3};
-        if (v) count_add(sc.counters, slot[threadIdx.x], v);
+    if (!join_chosen(sc)) return;
+    __shared__ TileWave waves[kJoinPairThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, xl = lane & 31;
+    TileWave &me = waves[wave];
+    const uint32_t entries = static_cast<uint32_t>(tab.join_blocks * n);
+    const uint32_t base =
+        ((blockIdx.x - build_blocks) * (kJoinPairThreads / 64) + static_cast<uint32_t>(wave)) * 64;
+    const uint32_t p = base + static_cast<uint32_t>(lane);
+    const int maxf = tab.max_flip;
+    uint32_t bs = 0, m = 0, i = 0;
+    int b = 0;
+    if (p < entries) {
+        const unsigned long long r = sc.jrange[p];
+        bs = static_cast<uint32_t>(r);
+        m = static_cast<uint32_t>(r >> 32) & 0xFFFFu;
+        b = static_cast<int>(r >> 48);
+        i = sc.jent[p];
     }
+    const bool grouped = m >= 2;
+    const uint64_t rows = __ballot(grouped);
+    uint32_t lo = grouped ? bs : 0xFFFFFFFFu, hi = grouped ? bs + m : 0u;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const uint32_t l2 = __shfl_xor(lo, off), h2 = __shfl_xor(hi, off);
+        lo = l2 < lo ? l2 : lo;
+        hi = h2 > hi ? h2 : hi;
+    }
+    me.key[lane] = grouped ? sc.jkeys[2 * static_cast<int64_t>(p)] : 0ull;
+    me.range[lane] = make_uint2(bs, grouped ? m | (static_cast<uint32_t>(b) << 16) : 0u);
+    me.who[lane] = i;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    Acc2 acc[2];
+    bool got = false;
+    unsigned long long n_cand = grouped ? m - 1 : 0, n_probe = 0, n_hit = 0, n_term = 0;
+    // bit strings as FP4 +-1, qubits 4 k + c of a half in nibble k of word c
+    auto signs = [](uint32_t v) {
+        v8i r = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            r[c] = static_cast<int>(((v << (3 - c)) & 0x88888888u) | 0x22222222u);
+        return r;
+    };
+    auto flush = [&](uint32_t cnt) {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        bool hit = false;
+        uint32_t x = 0;
+        double re = 0.0, im = 0.0;
+        if (lane < static_cast<int>(cnt)) {
+            const uint32_t e = me.q[lane], col = e >> 6;
+            x = e & 63u;
+            const uint2 g = me.range[x];
+            if (col - g.x < (g.y & 0xFFFFu) && col != base + x) {
+                const Key<1> xk{{me.key[x]}}, yk{{sc.jkeys[2 * static_cast<int64_t>(col)]}};
+                const Key<1> d{{xk.w[0] ^ yk.w[0]}};
+                if (first_agreeing<1>(tab, d) == static_cast<int>(g.y >> 16)) {
+                    if (d.w[0] == 0ull) {
+                        latch(sc.err, NQS_E_DUPLICATE);
+                    } else {
+                        ++n_probe;
+                        const int64_t xi = me.who[x];
+                        hit = join_hit<1, false, P, SCV>(
+                            tab, xk, yk, d, xi, static_cast<int32_t>(sc.jent[col]), log_amp[xi],
+                            phase[xi], log_amp, phase, nullptr, nullptr, 0, &n_term, re, im);
+                        n_hit += hit ? 1 : 0;
+                    }
+                }
+            }
+        }
+        if (__ballot(hit) == 0ull) return;
+        me.con[0][lane] = re;
+        me.con[1][lane] = im;
+        me.own[lane] = 0ull;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        if (hit) atomicOr(&me.own[x], 1ull << lane);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        unsigned long long mine = me.own[lane];
+        got |= mine != 0ull;
+        while (mine) {
+            const int k = __builtin_ctzll(mine);
+            mine &= mine - 1;
+            acc[0].add(me.con[0][k]);
+            acc[1].add(me.con[1][k]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    };
+    if (rows) {
+        const uint32_t *__restrict__ half_keys =
+            reinterpret_cast<const uint32_t *>(sc.jkeys) + half;
+        v8i xo[2];
+        uint32_t x_in = 0;  // bits of the halves whose row has partners
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint64_t k = me.key[32 * h + xl];
+            xo[h] = signs(static_cast<uint32_t>(k >> (32 * half)));
+            if ((rows >> (32 * h + xl)) & 1ull) x_in |= 0xFFFFu << (16 * (1 - h));
+        }
+        const float thr = 0.5f - static_cast<float>(64 - 2 * maxf);
+        v16f cthr;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) cthr[v] = thr;
+        uint32_t qn = 0;
+        auto column = [&](uint32_t t) {
+            const uint32_t c = t + static_cast<uint32_t>(xl);
+            return half_keys[4 * static_cast<int64_t>(c < hi ? c : hi - 1)];
+        };
+        uint32_t next = column(lo);
+        for (uint32_t t = lo; t < hi; t += 32) {
+            const v8i yo = signs(next);
+            next = column(t + 32);
+            v16f c[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                c[h] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(yo, xo[h], cthr, 4, 4, 0, 0,
+                                                                       0, 0);
+            float mx = c[0][0];
+#pragma unroll
+            for (int v = 1; v < 32; v += 2) {
+                const int w = v + 1 < 32 ? v + 1 : v;
+                mx = fmaxf(fmaxf(mx, c[v >> 4][v & 15]), c[w >> 4][w & 15]);
+            }
+            if (__ballot(mx > 0.0f) == 0ull) continue;
+            // bit 31 - v: value v = 16 h + r is positive (row 32 h + lane % 32,
+            // column t + 8 (r / 4) + 4 (lane / 32) + r % 4)
+            uint32_t neg = 0;
+#pragma unroll
+            for (int v = 0; v < 32; ++v)
+                neg = (neg << 1) | (__float_as_uint(c[v >> 4][v & 15]) >> 31);
+            uint32_t near = ~neg & x_in;
+            for (;;) {
+                const uint64_t any = __ballot(near != 0u);
+                if (!any) break;
+                if (near) {
+                    const uint32_t v = static_cast<uint32_t>(__builtin_clz(near));
+                    near &= ~(0x80000000u >> v);
+                    const uint32_t col = t + 8 * ((v & 15u) >> 2) +
+                                         4 * static_cast<uint32_t>(half) + (v & 3u);
+                    me.q[qn + lanes_below(any)] =
+                        (static_cast<uint32_t>(xl) + 32 * (v >> 4)) | (col << 6);
+                }
+                qn += static_cast<uint32_t>(__popcll(any));
+                if (qn >= 64) {
+                    flush(64);
+                    qn -= 64;
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                    if (lane < static_cast<int>(qn)) me.q[lane] = me.q[64 + lane];
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                }
+            }
+        }
+        if (qn) flush(qn);
+        if (got) {
+            const int64_t e = static_cast<int64_t>(b) * n + i;
+            *reinterpret_cast<double2 *>(sc.part + 2 * e) =
+                make_double2(acc[0].value(), acc[1].value());
+            atomicOr(&sc.jhit[e >> 5], 1u << (e & 31));
+        }
+    }
+    pair_counters(sc, n_cand, n_probe, n_hit, n_term);
+}
+
+int shortest_block(const DevTable &tab) {
+    int qmin = 128;
+    for (int b = 0; b < tab.join_blocks; ++b) {
+        const int q = __builtin_popcountll(tab.jmask[b][0]) + __builtin_popcountll(tab.jmask[b][1]);
+        qmin = q < qmin ? q : qmin;
+    }
+    return qmin;
+}
+
+// Whether the groups of a batch are compared as matrix tiles (see
+// kJoinTileGroup); debug dumps take the pair kernel.
+bool join_as_tiles(const DevTable &tab, int64_t n) {
+    const int qmin = shortest_block(tab);
+    return tab.n_qubits <= 63 && qmin < 62 && (n >> qmin) >= kJoinTileGroup;
 }
 
 template <int W>
@@ -667,7 +911,8 @@ hipError_t launch_join_prep_w(const DevTable &tab, const DevScratch &sc,
                        weights, n);
     hipLaunchKernelGGL(join_sort_kernel<W>, dim3(static_cast<unsigned>(sc.join_parts)),
                        dim3(kJoinSortThreads), 0, st, tab, sc, samples);
-    hipLaunchKernelGGL(join_decide_kernel, dim3(1), blk, 0, st, tab, sc, samples, n, g_eff);
+    hipLaunchKernelGGL(join_decide_kernel, dim3(1), blk, 0, st, tab, sc, samples, n, g_eff,
+                       join_as_tiles(tab, n));
     return hipGetLastError();
 }
 
@@ -679,15 +924,20 @@ hipError_t launch_pairs_w(const DevTable &tab, const DevScratch &sc, const uint6
     const int64_t entries = static_cast<int64_t>(tab.join_blocks) * n;
     const unsigned build_blocks =
         build ? static_cast<unsigned>((n + kJoinPairThreads - 1) / kJoinPairThreads) : 0u;
+    if constexpr (W == 1 && !D) {
+        if (join_as_tiles(tab, n)) {
+            const dim3 tgrid(build_blocks + static_cast<unsigned>((entries + kJoinPairThreads - 1) /
+                                                                  kJoinPairThreads));
+            hipLaunchKernelGGL((join_tile_kernel<P, SCV>), tgrid, dim3(kJoinPairThreads), 0, st,
+                               tab, sc, samples, weights, log_amp, phase, n, build_blocks);
+            return hipGetLastError();
+        }
+    }
     // several entries a lane where most samples are alone in their groups:
     // blocks whose contents outnumber the samples (fewer waves, each
     // gathering its few entries with partners); one a lane where blocks
     // are short and groups large (every entry has work: parallelism first)
-    int qmin = 128;
-    for (int b = 0; b < tab.join_blocks; ++b) {
-        const int q = __builtin_popcountll(tab.jmask[b][0]) + __builtin_popcountll(tab.jmask[b][1]);
-        qmin = q < qmin ? q : qmin;
-    }
+    const int qmin = shortest_block(tab);
     const int per = (qmin >= 62 || (int64_t(1) << qmin) >= 2 * n) ? kJoinPairPer : 1;
     const int64_t per_block = int64_t(kJoinPairThreads) * per;
     const dim3 grid(build_blocks + static_cast<unsigned>((entries + per_block - 1) / per_block));

@@ -2593,7 +2593,10 @@ bool pairs_cheaper(const DevTable &tab, int64_t n) {
     const double cost = dn * dn * ((n > kPairsWide ? 0.055 : 0.09) + 2.0 * tab.near_share);
     if (!tab.enum_ok) return cost < 1.2 * dn * static_cast<double>(tab.n_groups) + 4.0e7;
     const double hits = dn * tab.half_flips * std::fmin(1.0, dn / tab.half_states);
-    return cost + 35.0 * hits < 0.47 * dn * tab.half_flips + 150.0 * hits + 6.0e7;
+    // (a probe of a filter in class partitions costs about four: each round
+    // walks them; 40 qubits, 200,000 gathered samples 12.0 ms enumerated)
+    const double probe = 16 * n > (int64_t(1) << 20) ? 4.0 * 0.47 : 0.47;
+    return cost + 35.0 * hits < probe * dn * tab.half_flips + 150.0 * hits + 6.0e7;
 }
 }  // namespace
 
