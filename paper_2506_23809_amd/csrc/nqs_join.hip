@@ -50,7 +50,6 @@ namespace nqs {
 
 namespace {
 
-typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int kJoinGroupThreads = 1024;  // tile kernels
@@ -511,7 +510,7 @@ __device__ __forceinline__ bool join_hit(const DevTable &tab, const Key<W> &x, c
         } else {
             hsum = group_sum<W, DUMP>(tab, g, x, row, terms, cnt);
         }
-        const double2 rat = amp_ratio_f64(log_amp[j] - la, phase[j] - ph);
+        const double2 rat = amp_ratio_f64(log_amp[j], phase[j], la, ph);
         re = hsum * rat.x;
         im = hsum * rat.y;
     } else {
@@ -748,14 +747,6 @@ __global__ __launch_bounds__(kJoinPairThreads, 4) void join_tile_kernel(
     Acc2 acc[2];
     bool got = false;
     unsigned long long n_cand = grouped ? m - 1 : 0, n_probe = 0, n_hit = 0, n_term = 0;
-    // bit strings as FP4 +-1, qubits 4 k + c of a half in nibble k of word c
-    auto signs = [](uint32_t v) {
-        v8i r = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            r[c] = static_cast<int>(((v << (3 - c)) & 0x88888888u) | 0x22222222u);
-        return r;
-    };
     auto flush = [&](uint32_t cnt) {
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         bool hit = false;
@@ -807,7 +798,7 @@ __global__ __launch_bounds__(kJoinPairThreads, 4) void join_tile_kernel(
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const uint64_t k = me.key[32 * h + xl];
-            xo[h] = signs(static_cast<uint32_t>(k >> (32 * half)));
+            xo[h] = fp4_signs(static_cast<uint32_t>(k >> (32 * half)));
             if ((rows >> (32 * h + xl)) & 1ull) x_in |= 0xFFFFu << (16 * (1 - h));
         }
         const float thr = 0.5f - static_cast<float>(64 - 2 * maxf);
@@ -821,7 +812,7 @@ __global__ __launch_bounds__(kJoinPairThreads, 4) void join_tile_kernel(
         };
         uint32_t next = column(lo);
         for (uint32_t t = lo; t < hi; t += 32) {
-            const v8i yo = signs(next);
+            const v8i yo = fp4_signs(next);
             next = column(t + 32);
             v16f c[2];
 #pragma unroll

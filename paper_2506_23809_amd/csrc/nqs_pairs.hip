@@ -9,7 +9,9 @@
 // x . y = n_qubits - 2 distance(x, y): a tile of 32 x 32 pairs is one FP4
 // matrix product per 64 qubits (products of +-1 summed in FP32, exact), the
 // threshold sits in its C operand, and a pair is near where the result is
-// positive.  Near pairs (the group index decides whether X = x ^ y is a flip
+// positive.  The order of the qubits does not matter to the product, so the
+// operands are made from the bit strings by a shift and a mask per eight
+// qubits, where they are loaded.  Near pairs (the group index decides whether X = x ^ y is a flip
 // of the table) are queued per wave and evaluated 64 at a time, the few
 // groups with many terms (single excitations) in a queue of their own, so
 // that a wave's lanes run alike.
@@ -29,8 +31,6 @@ namespace nqs {
 
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int kPairsThreads = 512;
@@ -41,62 +41,43 @@ constexpr int kPairsQueue = 128;  // entries per queue and wave (64 are taken at
 // single excitations 2 n_qubits - 2 and an occupation row).
 constexpr uint32_t kShortTerms = 12;
 
+// A sample: its bits and, in FP64, its amplitude (the row's: its inverse), in
+// FP32 its log-amplitude and phase.
 struct alignas(16) PairRec {
     uint64_t w0, w1;
-    double la, ph;
+    double a, b;
 };
 
-// Bits of v as 32 nibbles of FP4 +1 (0x2) or -1 (0xA), 0 where valid is 0.
-__device__ __forceinline__ v4i fp4_signs(uint32_t v, uint32_t valid) {
-    v4i r;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        uint32_t b = (~v >> (8 * k)) & 0xFFu, m = (valid >> (8 * k)) & 0xFFu;
-        // one bit per nibble
-        b = (b | (b << 12)) & 0x000F000Fu;
-        b = (b | (b << 6)) & 0x03030303u;
-        b = (b | (b << 3)) & 0x11111111u;
-        m = (m | (m << 12)) & 0x000F000Fu;
-        m = (m | (m << 6)) & 0x03030303u;
-        m = (m | (m << 3)) & 0x11111111u;
-        r[k] = static_cast<int>(((b << 3) & (m << 3)) | (m << 1));
-    }
-    return r;
+inline bool pairs_f32(const DevTable &tab, int precision, bool dump) {
+    return precision == NQS_FP32_KAHAN && !dump && !tab.sc;
 }
 
 // Clears the counters and control words of the launch, makes the sample
 // checks of the hash build, and lays out the samples for the pair kernel:
-// the FP4 operand of each 32-sample tile (lane L of k-block kb: sample
-// L % 32, qubits 64 kb + 32 (L / 32) .. + 31) and one 32-byte record per
-// sample.
-template <int W>
+// one 32-byte record each, in FP64 the inverse amplitudes, and the bits by
+// tiles (4.1 us for 4,096 samples, 0.5 of them the amplitudes).
 __global__ __launch_bounds__(256) void pairs_prep_kernel(
     DevTable tab, DevScratch sc, const uint64_t *__restrict__ samples,
     const int64_t *__restrict__ weights, const double *__restrict__ log_amp,
-    const double *__restrict__ phase, int64_t n, uint32_t jparts, uint32_t jhit_words) {
+    const double *__restrict__ phase, int64_t n, bool f32, uint32_t jparts,
+    uint32_t jhit_words) {
     const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s < static_cast<uint32_t>(kCounters * kCounterSlots)) sc.counters[s] = 0;
     if (s == 0) *sc.mixed = 0;
     if (sc.jctl && s < static_cast<uint32_t>(kJoinCtl)) sc.jctl[s] = 0;
     if (s < jparts) sc.jcnt[s] = 0u;
     if (s < jhit_words) sc.jhit[s] = 0u;
-    const int64_t tiles = (n + 31) / 32;
     const int nq = tab.n_qubits;
-    if (s < tiles * W * 64) {
-        const int lane = static_cast<int>(s & 63u);
-        const int64_t tk = s >> 6;
-        const int kb = W == 2 ? static_cast<int>(tk & 1) : 0;
-        const int64_t i = (W == 2 ? tk >> 1 : tk) * 32 + (lane & 31);
-        v4i r = {0, 0, 0, 0};
-        if (i < n) {
-            const int q0 = 64 * kb + 32 * (lane >> 5);
-            const int left = nq - q0;
-            const uint32_t valid =
-                left >= 32 ? 0xFFFFFFFFu : (left <= 0 ? 0u : (1u << left) - 1u);
-            r = fp4_signs(static_cast<uint32_t>(samples[2 * i + kb] >> (32 * (lane >> 5))),
-                          valid);
+    // the bits of each tile of 32 samples, as the pair kernel's lanes read
+    // them: 64 qubits kb of sample xl at [tile][kb][half][xl]
+    if (s < (n + 31) / 32 * 32) {
+        const int words = nq <= 63 ? 1 : 2;
+        uint32_t *key = reinterpret_cast<uint32_t *>(sc.pkey) + (s >> 5) * words * 64 + (s & 31u);
+        for (int kb = 0; kb < words; ++kb) {
+            const uint64_t w = s < n ? samples[2 * static_cast<int64_t>(s) + kb] : 0ull;
+            key[64 * kb] = static_cast<uint32_t>(w);
+            key[64 * kb + 32] = static_cast<uint32_t>(w >> 32);
         }
-        reinterpret_cast<v4i *>(sc.pops)[s] = r;
     }
     if (s < n) {
         const int64_t i = s;
@@ -104,6 +85,12 @@ __global__ __launch_bounds__(256) void pairs_prep_kernel(
         const bool bad = nq >= 64 ? ((w1 >> (nq - 64)) != 0) : ((w0 >> nq) != 0 || w1 != 0);
         if (bad || (weights && weights[i] < 0)) latch(sc.err, NQS_E_RANGE);
         PairRec r{w0, w1, log_amp[i], phase[i]};
+        if (!f32) {
+            const double2 psi = psi_of(r.a, r.b);
+            r.a = psi.x;
+            r.b = psi.y;
+            reinterpret_cast<double2 *>(sc.pinv)[i] = psi_inverse(log_amp[i], phase[i]);
+        }
         reinterpret_cast<PairRec *>(sc.prec)[i] = r;
     }
 }
@@ -128,9 +115,11 @@ struct PairsWave {
 // (blockIdx.y); its waves take the tiles of y in turn.
 //
 // Bound: per 32 x 32 pairs one (W = 1) or two FP4 MFMAs of 32 cycles, about
-// ten VALU instructions where no pair is near and 1 KB W / H of operand from
-// the caches; per near pair the gathers of its record, group and values, and
-// the FP64 amplitude ratio (about 590 VALU instructions per 64 pairs).
+// ten VALU instructions where no pair is near, eight per 64 qubits to make
+// the operand and 256 bytes W / H of bits from the caches (as finished
+// operands 1 KB, no VALU instructions and no faster: 8,192 samples without a near
+// pair 12.0 and 11.5 us at 40 qubits, 11.7 and 12.6 at 100); per near pair the
+// gathers of its record, group and values.
 // Registers: 128 (four waves a SIMD); at 134 the 100-qubit form took 627 us
 // instead of 508 for 20,001 gathered samples, at 96 it spilled (600).
 template <int W, int H, bool DUMP, int P, bool SCV>
@@ -147,7 +136,19 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
     const PairRec *__restrict__ rec = reinterpret_cast<const PairRec *>(sc.prec);
     if (threadIdx.x < R) {
         const int64_t i = x0 + threadIdx.x;
-        xs[threadIdx.x] = i < n ? rec[i] : PairRec{0, 0, 0.0, 0.0};
+        // (no local record: the compiler would lay it out in LDS by the
+        // launch packet, in host memory: 12 us)
+        const int64_t at = i < n ? i : n - 1;
+        xs[threadIdx.x].w0 = rec[at].w0;
+        xs[threadIdx.x].w1 = rec[at].w1;
+        if constexpr (P == NQS_FP64) {
+            const double2 inv = reinterpret_cast<const double2 *>(sc.pinv)[at];
+            xs[threadIdx.x].a = inv.x;
+            xs[threadIdx.x].b = inv.y;
+        } else {
+            xs[threadIdx.x].a = rec[at].a;
+            xs[threadIdx.x].b = rec[at].b;
+        }
     }
     __syncthreads();
     PairsWave &me = waves[wave];
@@ -180,8 +181,8 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     };
     // <x|H|y> psi(y) / psi(x) of a pair whose group is g
-    auto evaluate = [&](const PairRec &x, const PairRec &y, int64_t i, int64_t g, uint32_t cnt,
-                        double &re, double &im) {
+    auto evaluate = [&](const PairRec &x, const PairRec &y, int64_t i, int64_t j, int64_t g,
+                        uint32_t cnt, double &re, double &im) {
         const Key<W> xk = rec_key<W>(x);
         if constexpr (P == NQS_FP64) {
             double h;
@@ -191,13 +192,15 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
                 uint32_t *row = (DUMP && sign_bits) ? sign_bits + i * sign_words : nullptr;
                 h = group_sum<W, DUMP>(tab, g, xk, row, &n_term, cnt);
             }
-            const double2 rat = amp_ratio_f64(y.la - x.la, y.ph - x.ph);
+            double2 rat = psi_product(make_double2(y.a, y.b), make_double2(x.a, x.b));
+            if (rat.x != rat.x)
+                rat = ratio_of_differences(log_amp[j] - log_amp[i], phase[j] - phase[i]);
             re = h * rat.x;
             im = h * rat.y;
         } else {
             const AccF32 h = group_sum_f32<W>(tab, g, xk, &n_term, cnt);
             float rr, ri;
-            ratio_f32(y.la - x.la, y.ph - x.ph, rr, ri);
+            ratio_f32(y.a - x.a, y.b - x.b, rr, ri);
             const float pre = h.s * rr, pim = h.s * ri;
             re = static_cast<double>(pre) + static_cast<double>(fmaf(h.s, rr, -pre) + h.c * rr);
             im = static_cast<double>(pim) + static_cast<double>(fmaf(h.s, ri, -pim) + h.c * ri);
@@ -212,7 +215,7 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
         if (on) {
             const uint2 e = me.lq[lane];
             x = e.x & 63u;
-            evaluate(xs[x], rec[e.x >> 6], x0 + x, e.y, 0u, re, im);
+            evaluate(xs[x], rec[e.x >> 6], x0 + x, e.x >> 6, e.y, 0u, re, im);
         }
         deposit(on, x, re, im);
     };
@@ -260,7 +263,7 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
                         ++n_hit;
                         later = SCV ? pop == 2 : cnt > kShortTerms;
                         now = !later;
-                        if (now) evaluate(xs[x], y, i, g, cnt, re, im);
+                        if (now) evaluate(xs[x], y, i, j, g, cnt, re, im);
                     }
                 }
             }
@@ -278,22 +281,20 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
     };
 
     // the x operands, resident; the C operand: near pairs come out positive
-    const v4i *__restrict__ ops = reinterpret_cast<const v4i *>(sc.pops);
+    const uint32_t *__restrict__ words = reinterpret_cast<const uint32_t *>(sc.pkey) + lane;
     const int tiles = static_cast<int>((n + 31) / 32);
-    auto operand = [&](int t, int kb) {
-        const v4i o = ops[(static_cast<int64_t>(t) * W + kb) * 64 + lane];
-        return v8i{o[0], o[1], o[2], o[3], 0, 0, 0, 0};
-    };
+    // half of the lane's sample of tile t, 32 qubits of k-block kb
+    auto column = [&](int t, int kb) { return words[(t * W + kb) * 64]; };
     v8i xo[H][W];
     uint32_t x_in = 0;  // bits of the halves whose sample exists
 #pragma unroll
     for (int h = 0; h < H; ++h) {
         const int t = static_cast<int>(blockIdx.x) * H + h;
 #pragma unroll
-        for (int kb = 0; kb < W; ++kb) xo[h][kb] = operand(t < tiles ? t : tiles - 1, kb);
+        for (int kb = 0; kb < W; ++kb) xo[h][kb] = fp4_signs(column(t < tiles ? t : tiles - 1, kb));
         if (x0 + 32 * h + xl < n) x_in |= 0xFFFFu << (16 * (H - 1 - h));
     }
-    const float thr = 0.5f - static_cast<float>(tab.n_qubits - 2 * tab.max_flip);
+    const float thr = 0.5f - static_cast<float>(64 * W - 2 * tab.max_flip);
     v16f cthr;
 #pragma unroll
     for (int r = 0; r < 16; ++r) cthr[r] = thr;
@@ -310,21 +311,24 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
         mine &= every << (t / step);
         t %= step;
     }
-    v8i next[W];
+    uint32_t next[W];
 #pragma unroll
-    for (int kb = 0; kb < W; ++kb) next[kb] = operand(t < tiles ? t : tiles - 1, kb);
+    for (int kb = 0; kb < W; ++kb) next[kb] = column(t < tiles ? t : tiles - 1, kb);
     for (; t < tiles; t += step) {
         v16f c[H];
+        v8i yo[W];
+#pragma unroll
+        for (int kb = 0; kb < W; ++kb) yo[kb] = fp4_signs(next[kb]);
 #pragma unroll
         for (int h = 0; h < H; ++h) {
             c[h] = cthr;
 #pragma unroll
             for (int kb = 0; kb < W; ++kb)
-                c[h] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(next[kb], xo[h][kb], c[h], 4,
+                c[h] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(yo[kb], xo[h][kb], c[h], 4,
                                                                        4, 0, 0, 0, 0);
         }
 #pragma unroll
-        for (int kb = 0; kb < W; ++kb) next[kb] = operand(t + step < tiles ? t + step : t, kb);
+        for (int kb = 0; kb < W; ++kb) next[kb] = column(t + step < tiles ? t + step : t, kb);
         float mx = c[0][0];
 #pragma unroll
         for (int v = 1; v < 16 * H; v += 2) {
@@ -412,47 +416,36 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
                   static_cast<unsigned long long>(n) * static_cast<unsigned long long>(n - 1));
 }
 
-template <int W>
-hipError_t launch_prep_w(const DevTable &tab, const DevScratch &sc, const uint64_t *samples,
-                         const int64_t *weights, const double *log_amp, const double *phase,
-                         int64_t n, hipStream_t st) {
-    const uint32_t jparts = sc.jctl ? static_cast<uint32_t>(sc.join_parts) : 0u;
-    const uint32_t jhw =
-        sc.jctl ? static_cast<uint32_t>((tab.join_blocks * n + 31) / 32) : 0u;
-    int64_t span = (n + 31) / 32 * W * 64;
-    const int64_t least[] = {kCounters * kCounterSlots, kJoinCtl, jparts, jhw, n};
-    for (int64_t v : least) span = v > span ? v : span;
-    hipLaunchKernelGGL(pairs_prep_kernel<W>, dim3(static_cast<unsigned>((span + 255) / 256)),
-                       dim3(256), 0, st, tab, sc, samples, weights, log_amp, phase, n, jparts, jhw);
-    return hipGetLastError();
-}
-
 }  // namespace
 
-size_t pairs_scratch_bytes(const DevTable &tab, int64_t n) {
-    const int words = tab.n_qubits <= 63 ? 1 : 2;
-    return static_cast<size_t>((n + 31) / 32) * 32 * 32 * words + sizeof(PairRec) * n;
-}
-
-void pairs_scratch_layout(const DevTable &tab, int64_t n, char *base, DevScratch *sc) {
-    const int words = tab.n_qubits <= 63 ? 1 : 2;
-    sc->pops = base;
-    sc->prec = base + static_cast<size_t>((n + 31) / 32) * 32 * 32 * words;
+// 32 + 16 + 8 or 16 bytes per sample, the last for whole tiles: within the
+// hash's 64 or 96 (128 slots at least).
+void pairs_scratch_layout(int64_t n, char *base, DevScratch *sc) {
+    sc->prec = base;
+    sc->pinv = base + sizeof(PairRec) * n;
+    sc->pkey = sc->pinv + sizeof(double2) * n;
 }
 
 hipError_t launch_pairs_prep(const DevTable &tab, const DevScratch &sc, const uint64_t *samples,
                              const int64_t *weights, const double *log_amp, const double *phase,
-                             int64_t n, hipStream_t st) {
-    return tab.n_qubits <= 63
-               ? launch_prep_w<1>(tab, sc, samples, weights, log_amp, phase, n, st)
-               : launch_prep_w<2>(tab, sc, samples, weights, log_amp, phase, n, st);
+                             int64_t n, int precision, bool dump, hipStream_t st) {
+    const uint32_t jparts = sc.jctl ? static_cast<uint32_t>(sc.join_parts) : 0u;
+    const uint32_t jhw =
+        sc.jctl ? static_cast<uint32_t>((tab.join_blocks * n + 31) / 32) : 0u;
+    int64_t span = (n + 31) / 32 * 32;
+    const int64_t least[] = {kCounters * kCounterSlots, kJoinCtl, jparts, jhw};
+    for (int64_t v : least) span = v > span ? v : span;
+    hipLaunchKernelGGL(pairs_prep_kernel, dim3(static_cast<unsigned>((span + 255) / 256)),
+                       dim3(256), 0, st, tab, sc, samples, weights, log_amp, phase, n,
+                       pairs_f32(tab, precision, dump), jparts, jhw);
+    return hipGetLastError();
 }
 
 hipError_t launch_pairs(const DevTable &tab, const DevScratch &sc, const double *log_amp,
                         const double *phase, int64_t n, int precision, int32_t *hit_idx,
                         uint32_t *sign_bits, int64_t sign_words, hipStream_t st) {
     const bool dump = hit_idx || sign_bits;
-    const bool f32 = precision == NQS_FP32_KAHAN && !dump && !tab.sc;
+    const bool f32 = pairs_f32(tab, precision, dump);
     const bool wide = n > kPairsWide;
     const int64_t rows = wide ? 64 : 32;
     const dim3 grid(static_cast<unsigned>((n + rows - 1) / rows),
