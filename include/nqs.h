@@ -326,7 +326,8 @@ int nqs_last_kernel_ms(nqs_ham h, float out[3]);
 /*
  * Finer durations of the last profiled evaluation, in milliseconds, from
  * the same events plus two more (stages that did not run take ~0):
- *   out[0] clear and the pair join's grouping (bucket keys, fingerprints
+ *   out[0] clear (the layout of the samples where all pairs are compared)
+ *          and the pair join's grouping (bucket keys, fingerprints
  *          and the sample checks and, in the same launch, the hash clear;
  *          partition counts, placing, per-partition sort, the device's
  *          decision)
@@ -334,9 +335,10 @@ int nqs_last_kernel_ms(nqs_ham h, float out[3]);
  *          runs inside the pair kernel's launch)
  *   out[2] the pair join's pair kernel (with the hash build, except in a
  *          launch that only joins)
- *   out[3] enumeration / streaming lookup kernels (return at once when the
- *          join runs)
- *   out[4] finish kernel (diagonal + partial sums)
+ *   out[3] comparison of all pairs, or enumeration / streaming lookup
+ *          kernels (return at once when the join runs)
+ *   out[4] finish kernel (diagonal + partial sums; of up to 512 samples in
+ *          nqs_eloc_energy also the energy)
  *   out[5] all of the evaluation
  * Errors as nqs_last_kernel_ms.
  */

@@ -2048,6 +2048,31 @@ __device__ void energy_block_partial(double w, double re, double im, double *__r
     }
 }
 
+// Eq. 1's result {mean re, mean im, variance, sum w} from the sums (by one
+// thread).  out may be pinned host memory; with err, the device's error word
+// is copied to *err_out beside it (the host reads both after one wait).
+__device__ void energy_publish(double SW, double SR, double SI, double SV,
+                               double *__restrict__ out, const int *__restrict__ err,
+                               int *__restrict__ err_out, unsigned *__restrict__ seq,
+                               unsigned *__restrict__ seq_out,
+                               const unsigned long long *__restrict__ jctl,
+                               unsigned *__restrict__ chosen_out) {
+    out[0] = SW != 0.0 ? SR / SW : 0.0;
+    out[1] = SW != 0.0 ? SI / SW : 0.0;
+    out[2] = SW != 0.0 ? SV / SW : 0.0;
+    out[3] = SW;
+    if (err) *err_out = *err;
+    if (chosen_out) *chosen_out = jctl ? (jctl[kJoinCtlChosen] != 0ull ? 1u : 0u) : 2u;
+    if (seq) {
+        // a new sequence number, published after the results (system
+        // scope: the host polls it)
+        const unsigned v = *seq + 1u;
+        *seq = v;
+        __threadfence_system();
+        *reinterpret_cast<volatile unsigned *>(seq_out) = v;
+    }
+}
+
 template <int W, bool DUMP, int P, bool SCV>
 __global__ __launch_bounds__(256) void eloc_finish_kernel(
     DevTable tab, DevScratch sc, const uint64_t *__restrict__ samples, int64_t n,
@@ -2100,13 +2125,17 @@ __global__ __launch_bounds__(256) void eloc_finish_kernel(
 // dump): the digit tiles staged in LDS once per block, the
 // diagonal of each wave's 64 samples on the matrix cores, then the partials.
 constexpr int kFinishMfmaThreads = 1024;
+// Largest batch finished by one block, which then combines the energy too:
+// a launch and its gap less, against the waves of one CU (a step of 500
+// samples 39.5 us with the combining launch and 35.9 without, 32 qubits; of
+// 1,000 36.4 and 39.6, 40 qubits).
+constexpr int kFinishAlone = 512;
 constexpr int kDiagMaxTiles = diag_mfma_tiles(8);
 
 template <int W, int P>
 __global__ __launch_bounds__(kFinishMfmaThreads) void eloc_finish_mfma_kernel(
     DevTable tab, DevScratch sc, const uint64_t *__restrict__ samples, int64_t n,
-    int64_t n_chunks, int enum_on, double *__restrict__ eloc, const int64_t *__restrict__ weights,
-    double *__restrict__ epart) {
+    int64_t n_chunks, int enum_on, double *__restrict__ eloc, EnergyFused ef, bool alone) {
     __shared__ diag_v4i tiles[kDiagMaxTiles * kDiagLimbs * 64];
     // the sample first: its load overlaps the staging of the tiles
     Key<W> x;
@@ -2129,10 +2158,19 @@ __global__ __launch_bounds__(kFinishMfmaThreads) void eloc_finish_mfma_kernel(
     finish_one<W, false, P, false>(tab, sc, samples, n, n_chunks, enum_on != 0, eloc, nullptr,
                                    nullptr, 0, i, nullptr, nullptr, 0, nullptr, nullptr, true, d,
                                    &v);
-    if (epart) {
+    if (ef.part) {
         // this thread's E_loc, as just written (not read back)
-        energy_block_partial(i < n ? static_cast<double>(weights[i]) : 0.0, v.x, v.y,
-                             epart + 4 * static_cast<int64_t>(blockIdx.x));
+        double *part = ef.part + 4 * static_cast<int64_t>(blockIdx.x);
+        energy_block_partial(i < n ? static_cast<double>(ef.weights[i]) : 0.0, v.x, v.y, part);
+        // the only block has the whole sums (no combining launch): its E_loc
+        // is out before the host sees the result
+        if (alone) {
+            __threadfence_system();
+            __syncthreads();
+            if (threadIdx.x == 0)
+                energy_publish(part[0], part[1], part[2], part[3], ef.out, sc.err, ef.err_out,
+                               ef.seq, ef.seq_out, sc.jctl, ef.chosen_out);
+        }
     }
 }
 
@@ -2505,8 +2543,6 @@ __global__ __launch_bounds__(kRedThreads) void energy_block_kernel(
 
 // Single block: out = {mean re, mean im, variance, sum w} from nb block
 // partials (thread t takes partials t, t + kRedThreads, ... in that order).
-// out may be pinned host memory; with err, the device's error word is
-// copied to *err_out beside it (the host reads both after one wait).
 __global__ __launch_bounds__(kRedThreads) void energy_combine_kernel(
     const double *__restrict__ part, int64_t nb, double *__restrict__ out,
     const int *__restrict__ err, int *__restrict__ err_out, unsigned *__restrict__ seq,
@@ -2531,22 +2567,8 @@ __global__ __launch_bounds__(kRedThreads) void energy_combine_kernel(
         }
     }
     const double SV = block_sum(c, lds);
-    if (threadIdx.x == 0) {
-        out[0] = MR;
-        out[1] = MI;
-        out[2] = SW != 0.0 ? SV / SW : 0.0;
-        out[3] = SW;
-        if (err) *err_out = *err;
-        if (chosen_out) *chosen_out = jctl ? (jctl[kJoinCtlChosen] != 0ull ? 1u : 0u) : 2u;
-        if (seq) {
-            // a new sequence number, published after the results (system
-            // scope: the host polls it)
-            const unsigned v = *seq + 1u;
-            *seq = v;
-            __threadfence_system();
-            *reinterpret_cast<volatile unsigned *>(seq_out) = v;
-        }
-    }
+    if (threadIdx.x == 0)
+        energy_publish(SW, SR, SI, SV, out, err, err_out, seq, seq_out, jctl, chosen_out);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -2926,27 +2948,31 @@ hipError_t launch_eloc(const DevTable &tab, const DevScratch &sc, const EvalLaun
         // has it too: its sum over occupied pairs took 53 us of 8,193 samples
         // at 40 qubits)
         // 1024-thread blocks once they fill every CU (each block stages the
-        // digit tiles once), else 256-thread blocks to spread a small batch
-        const int mth = n >= 256 * int64_t(kFinishMfmaThreads) ? kFinishMfmaThreads : 256;
+        // digit tiles once), else 256-thread blocks to spread a small batch;
+        // a batch of one block combines the energy itself
+        const bool alone = ef.part && n <= kFinishAlone;
+        const int mth = n >= 256 * int64_t(kFinishMfmaThreads)
+                            ? kFinishMfmaThreads
+                            : (alone ? static_cast<int>((n + 63) / 64 * 64) : 256);
         const dim3 mgrid(static_cast<unsigned>((n + mth - 1) / mth));
         const dim3 mblk(mth);
         if (words == 1) {
             if (f32)
                 hipLaunchKernelGGL((eloc_finish_mfma_kernel<1, NQS_FP32_KAHAN>), mgrid, mblk, 0,
-                                   st, tab, sc, samples, n, chunks, fb, eloc, ef.weights, ef.part);
+                                   st, tab, sc, samples, n, chunks, fb, eloc, ef, alone);
             else
                 hipLaunchKernelGGL((eloc_finish_mfma_kernel<1, NQS_FP64>), mgrid, mblk, 0, st, tab,
-                                   sc, samples, n, chunks, fb, eloc, ef.weights, ef.part);
+                                   sc, samples, n, chunks, fb, eloc, ef, alone);
         } else {
             if (f32)
                 hipLaunchKernelGGL((eloc_finish_mfma_kernel<2, NQS_FP32_KAHAN>), mgrid, mblk, 0,
-                                   st, tab, sc, samples, n, chunks, fb, eloc, ef.weights, ef.part);
+                                   st, tab, sc, samples, n, chunks, fb, eloc, ef, alone);
             else
                 hipLaunchKernelGGL((eloc_finish_mfma_kernel<2, NQS_FP64>), mgrid, mblk, 0, st, tab,
-                                   sc, samples, n, chunks, fb, eloc, ef.weights, ef.part);
+                                   sc, samples, n, chunks, fb, eloc, ef, alone);
         }
         if (ev.after_finish && (e = hipEventRecord(ev.after_finish, st)) != hipSuccess) return e;
-        if (ef.part)
+        if (ef.part && !alone)
             hipLaunchKernelGGL(energy_combine_kernel, dim3(1), dim3(kRedThreads), 0, st, ef.part,
                                static_cast<int64_t>(mgrid.x), ef.out, sc.err, ef.err_out, ef.seq,
                                ef.seq_out, sc.jctl, ef.chosen_out);
