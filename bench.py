@@ -41,14 +41,27 @@ FP64_PEAK_ADDS = 256 * 4 * 16 * 2.4e9
 CSRC = os.path.join(ROOT, "paper_2506_23809_amd", "csrc")
 # int8 dense MFMA peak of MI355X (5.0 POP/s)
 INT8_PEAK_OPS = 5.0e15
+# fp4 dense MFMA peak (10 POP/s)
+FP4_PEAK_OPS = 10.0e15
 PROFILES = os.path.join(ROOT, "profiles")
 
 
 def kernel_source_hash(kernel: str) -> str:
     """Hash of the source file that defines the kernel."""
-    src = "nqs_join.hip" if kernel.startswith("join_") else "nqs_kernels.hip"
+    src = ("nqs_join.hip" if kernel.startswith("join_") else
+           "nqs_pairs.hip" if kernel.startswith("pairs_") else "nqs_kernels.hip")
     with open(os.path.join(CSRC, src), "rb") as f:
         return hashlib.sha256(f.read()).hexdigest()[:16]
+
+
+def strategy_of(plan, st, n):
+    """The strategy that evaluated a batch of n, from its plan and counts."""
+    if plan["join_ran"] == 1:
+        return "pair join"
+    if st["enum_rounds"] > 0:
+        return "enumeration"
+    # the comparison of all pairs counts every ordered pair as a candidate
+    return "all pairs" if n > 1 and st["candidates"] == n * (n - 1) else "streaming"
 
 
 def algorithmic_bytes(n_s, words, n_groups, n_terms, probes, hits, hit_terms):
@@ -307,7 +320,7 @@ def main():
     plan = ham.plan()
     joined = plan.get("join_ran") == 1
     enumerated = st.get("enum_rounds", 0) > 0
-    strategy = "pair join" if joined else ("enumeration" if enumerated else "streaming")
+    strategy = strategy_of(plan, st, w.n_samples)
     n_occ = w.n_alpha + w.n_beta
     occ_form = True  # every molecular table has the occupation-form diagonal
     finish_name = "eloc_finish_mfma_kernel" if occ_form else "eloc_finish_kernel"
@@ -318,6 +331,8 @@ def main():
         kernels = {"join_pair_kernel": pair_ms, finish_name: finish_ms}
     elif enumerated:
         kernels = {"eloc_enum_kernel": lookup_ms, finish_name: finish_ms}
+    elif strategy == "all pairs":
+        kernels = {"pairs_kernel": lookup_ms, finish_name: finish_ms}
     else:
         kernels = {"eloc_lookup_kernel": lookup_ms, finish_name: finish_ms}
     kernel_name = max(kernels, key=kernels.get)
@@ -341,6 +356,14 @@ def main():
         unit_name = "entry (sample, block): 48 B; candidate pair inside a group: 24 B"
         b_pair = algorithmic_bytes_join_pairs(entries, st["candidates"])
         achieved = b_pair / (kernel_ms / 1e3)
+    elif kernel_name == "pairs_kernel":
+        # one FP4 product of +-1 per qubit and ordered pair
+        bound, unit = "mfma", "TOP/s (fp4, dense)"
+        peak = FP4_PEAK_OPS
+        per_unit = 2 * w.n_qubits
+        units = st["candidates"]
+        unit_name = "ordered pair of samples (a multiply-add per qubit, x2)"
+        achieved = per_unit * units / (kernel_ms / 1e3)
     elif kernel_name == "eloc_enum_kernel":
         bound, unit = "alu", "Tops/s (int32 VALU lane-ops)"
         peak = VALU_PEAK_OPS
@@ -525,8 +548,7 @@ def secondary(args, log, dev):
         pairs = st["pairs"]
         ms = float(np.mean(per))
         plan = ham.plan()
-        strategy = ("pair join" if plan["join_ran"] == 1 else
-                    ("enumeration" if st["enum_rounds"] > 0 else "streaming"))
+        strategy = strategy_of(plan, st, w.n_samples)
         out[w.name] = {"pair_evals_per_s": pairs / (ms / 1e3), "ms_per_step": ms,
                        "ms_per_step_median": float(np.median(per)),
                        "ms_per_step_min": float(np.min(per)), "steps": steps,

@@ -21,8 +21,8 @@
 // partition is sorted in LDS by (bucket, content fingerprint), and
 // the start and size of each entry's group (its bucket's members with its
 // fingerprint: hash-colliding contents mostly fall apart) are written beside
-// the entries.  The pair kernel then takes one lane per
-// entry, or compares large groups as matrix tiles.
+// the entries.  The pair kernel then takes one lane per entry; large groups
+// are compared as matrix tiles instead.
 //
 // Cost: the ordered pairs inside groups, the sum of squared group sizes.
 // For samples spread over a large sector this is far below the

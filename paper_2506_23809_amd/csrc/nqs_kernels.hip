@@ -2600,10 +2600,10 @@ constexpr int64_t kPairsDirect = 8192;
 // strategy beside the pair join: the enumeration of a half-filled sector, or
 // streaming.  Picoseconds on MI355X: a pair 0.09 (11.5 us for 8,192 samples
 // at 100 qubits, 5 of them the launch) or 0.055 in wide blocks (234 us for
-// 65,536), a connected pair 35 against 150 of the enumeration (37,843
-// gathered samples at 40 qubits with 17 M hits: 0.62 ms of kernel; 24 qubits,
-// 100,001 samples, 34 M hits: 1.63 against 7.8), a lookup of the enumeration 0.47 (70.9 ms for 1.5 10^11)
-// and 6 10^7 for the hash it needs, a streamed pair 1.2 (20,000 groups past
+// 65,536), a connected pair 30 to 35 against 150 of the enumeration (37,843
+// gathered samples at 40 qubits with 17 M hits: 0.49 ms of kernel; 24 qubits,
+// 100,001 samples, 34 M hits: 1.37 against 7.8), a lookup of the enumeration
+// 0.47 (70.9 ms for 1.5 10^11) and 6 10^7 for the hash it needs, a streamed pair 1.2 (20,000 groups past
 // 10,007 samples: 240 us); a near pair that the group index decides 2.
 bool pairs_cheaper(const DevTable &tab, int64_t n) {
     // (the pair kernel packs a sample's index in 27 bits)
