@@ -2603,14 +2603,25 @@ constexpr int64_t kPairsDirect = 8192;
 // 65,536), a connected pair 30 to 35 against 150 of the enumeration (37,843
 // gathered samples at 40 qubits with 17 M hits: 0.49 ms of kernel; 24 qubits,
 // 100,001 samples, 34 M hits: 1.37 against 7.8), a lookup of the enumeration
-// 0.47 (70.9 ms for 1.5 10^11) and 6 10^7 for the hash it needs, a streamed pair 1.2 (20,000 groups past
-// 10,007 samples: 240 us); a near pair that the group index decides 2.
+// 0.47 (70.9 ms for 1.5 10^11) and 6 10^7 for the hash it needs, a streamed pair 0.8 beside 1.15 10^8 of
+// its call (20,000 groups past 10,007 samples: 300 us, 500 past 3,619: 172).
+// Of a general table nearly every pair may be near, and the group index
+// decides it: 20, or 42 where its buckets are more than 0.4 full and a wave's
+// lookups go on to further ones.  All pairs and streaming, us: 26 qubits, 12
+// flips, 3,619 samples, 500 groups 260 and 172, 20,000 groups 129 and 300; 36
+// qubits, 10,007 samples, 500 groups 195 and 157, 20,000 205 and 305; 26
+// qubits, 10,007 samples, 20,000 groups 540 and 399.
 bool pairs_cheaper(const DevTable &tab, int64_t n) {
     // (the pair kernel packs a sample's index in 27 bits)
     if (n > kJoinMaxSamples) return false;
     const double dn = static_cast<double>(n);
-    const double cost = dn * dn * ((n > kPairsWide ? 0.055 : 0.09) + 2.0 * tab.near_share);
-    if (!tab.enum_ok) return cost < 1.2 * dn * static_cast<double>(tab.n_groups) + 4.0e7;
+    const double pair = n > kPairsWide ? 0.055 : 0.09, groups = static_cast<double>(tab.n_groups);
+    if (!tab.enum_ok) {
+        const double load = std::ldexp(groups, static_cast<int>(tab.gh_shift) - 32);
+        const double cost = dn * dn * (pair + (load > 0.4 ? 42.0 : 20.0) * tab.near_share);
+        return cost < 0.8 * dn * groups + 1.15e8;
+    }
+    const double cost = dn * dn * (pair + 2.0 * tab.near_share);
     const double hits = dn * tab.half_flips * std::fmin(1.0, dn / tab.half_states);
     // (a probe of a filter in class partitions costs about four: each round
     // walks them; 40 qubits, 200,000 gathered samples 12.0 ms enumerated)
