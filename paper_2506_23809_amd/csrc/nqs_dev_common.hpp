@@ -28,6 +28,19 @@ __device__ __forceinline__ Key<W> load_key(const uint64_t *__restrict__ p, int64
     return k;
 }
 
+// The bits of k below n_qubits.  A sample with others is latched as an error
+// but still compared with the rest of its batch, so whatever turns set bits
+// into indices of a table takes these alone.
+template <int W>
+__device__ __forceinline__ Key<W> in_register(const DevTable &tab, Key<W> k) {
+    if constexpr (W == 1) {
+        k.w[0] &= (1ull << tab.n_qubits) - 1ull;
+    } else {
+        k.w[W - 1] &= (1ull << (tab.n_qubits - 64)) - 1ull;
+    }
+    return k;
+}
+
 template <int W>
 __device__ __forceinline__ uint32_t linear_hash(const Key<W> &k, const uint32_t *__restrict__ hr) {
     uint32_t h = 0;
@@ -364,8 +377,9 @@ __device__ __forceinline__ double eri_at(const DevTable &tab, int p, int q, int 
 }
 
 template <int W>
-__device__ __forceinline__ double sc_element(const DevTable &tab, const Key<W> &bra,
-                                             const Key<W> &ket) {
+__device__ __forceinline__ double sc_element(const DevTable &tab, const Key<W> &b_any,
+                                             const Key<W> &k_any) {
+    const Key<W> bra = in_register<W>(tab, b_any), ket = in_register<W>(tab, k_any);
     Key<W> A, I;
     int na = 0, ni = 0;
 #pragma unroll
@@ -424,7 +438,8 @@ __device__ __forceinline__ double sc_element(const DevTable &tab, const Key<W> &
 }
 
 template <int W>
-__device__ __forceinline__ double sc_diagonal(const DevTable &tab, const Key<W> &x) {
+__device__ __forceinline__ double sc_diagonal(const DevTable &tab, const Key<W> &any) {
+    const Key<W> x = in_register<W>(tab, any);
     const int K = tab.sc_k;
     double d = 0.0;
 #pragma unroll
