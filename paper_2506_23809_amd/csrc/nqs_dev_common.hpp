@@ -631,10 +631,15 @@ __device__ __forceinline__ int64_t group_find(const DevTable &tab, const Key<W> 
 // Sum of FP64 values as an unevaluated pair hi + lo: the rounding errors of
 // the additions (TwoSum) go to lo, so the value, rounded once, does not
 // depend on the order of the additions (up to ties closer than about 2^-100
-// of the largest partial sum).  An infinity or NaN passes through hi.
+// of the largest partial sum).  An infinity or NaN passes through hi.  The
+// additions are kept apart from the product that v may be: contracted with it
+// in one copy of an unrolled loop and not in the next, they would add v in
+// one place and the unrounded product in the other, and the sum would depend
+// on which of them comes where.
 struct Acc2 {
     double hi = 0.0, lo = 0.0;
     __device__ __forceinline__ void add(double v) {
+#pragma clang fp contract(off)
         const double s = hi + v, bp = s - hi;
         lo += (hi - (s - bp)) + (v - bp);
         hi = s;
