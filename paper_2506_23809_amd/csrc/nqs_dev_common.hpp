@@ -290,7 +290,8 @@ __device__ __forceinline__ double group_sum(const DevTable &tab, int64_t g, cons
     if (!DUMP && value[2] != 0ull) {
         // occupied qubits four at a time (the last entry of a row is 0)
         const int nq = tab.n_qubits;
-        uint64_t lo = x.w[0], hi = W == 2 ? x.w[W - 1] : 0ull;
+        const Key<W> occ = in_register<W>(tab, x);
+        uint64_t lo = occ.w[0], hi = W == 2 ? occ.w[W - 1] : 0ull;
         int in = 0;  // flips of X that are occupied
 #pragma unroll
         for (int q = 0; q < W; ++q) in += __popcll(X.w[q] & x.w[q]);

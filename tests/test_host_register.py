@@ -160,3 +160,67 @@ def check(tmp_path, body):
 
 def test_integral_elements_stay_inside_their_tables(tmp_path):
     check(tmp_path, INTEGRALS)
+
+
+ROWS = r"""
+// one group of one or two flips whose strings differ from a base in one qubit
+// (an occupation row), the last piece of its table, and a tabulated one
+template <int W>
+static void run(int nq, int flips) {
+    std::vector<uint64_t> x, z;
+    std::vector<double> c;
+    const auto term = [&](uint64_t z0, uint64_t z1) {
+        uint64_t X[2] = {0, 0};
+        for (int f = 0; f < flips; ++f) X[(3 * f) >> 6] |= 1ull << (3 * f);
+        x.insert(x.end(), X, X + 2);
+        z.push_back(z0);
+        z.push_back(z1);
+        c.push_back(uniform());
+    };
+    for (int q = 0; q < nq; ++q)
+        if (q % 3 || q >= 3 * flips) term(q < 64 ? 1ull << q : 0, q < 64 ? 0 : 1ull << (q - 64));
+    HostTable T;
+    std::string err;
+    if (build_table(nq, static_cast<int64_t>(c.size()), x.data(), z.data(), c.data(), nullptr, &T, &err)) {
+        std::printf("%s\n", err.c_str());
+        ++bad;
+        return;
+    }
+    GroupRecords R;
+    build_group_records(T, &R);
+    expect(R.rows.size() == 2 * size_t(nq + 2), "one occupation row", nq);
+    const Guarded rows(R.rows, 256);
+    std::vector<uint32_t> goff(T.goff.begin(), T.goff.end());
+    DevTable tab{};
+    tab.n_qubits = nq;
+    tab.gx = R.rec.data();
+    tab.gx_stride = kGroupWords;
+    tab.goff = goff.data();
+    tab.tz = R.z.data();
+    tab.tc = T.tc.data();
+    tab.tcode = R.codes.data();
+    tab.occ = rows.data();
+    for (int k = 0; k < 2000; ++k) {
+        unsigned long long terms = 0;
+        const Key<W> s = sample<W>(nq, 0);
+        const double v = group_sum<W, false>(tab, 0, s, nullptr, &terms);
+        expect(v == v, "sum of a valid sample", nq);
+        expect(group_sum<W, false>(tab, 0, outside<W>(s, nq, rnd()), nullptr, &terms) == v,
+               "sum with stray bits", nq);
+        expect(group_sum<W, false>(tab, 0, outside<W>(s, nq, ~0ull), nullptr, &terms) == v,
+               "sum with all stray bits", nq);
+    }
+}
+int main() {
+    for (int f = 1; f <= 2; ++f) {
+        run<1>(12, f); run<1>(24, f); run<1>(62, f); run<1>(63, f);
+        run<2>(64, f); run<2>(66, f); run<2>(100, f); run<2>(127, f);
+    }
+    if (bad) std::printf("%d wrong\n", bad);
+    return bad != 0;
+}
+"""
+
+
+def test_occupation_rows_stay_inside_their_tables(tmp_path):
+    check(tmp_path, ROWS)
