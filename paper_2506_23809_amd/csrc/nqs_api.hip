@@ -153,6 +153,7 @@ nqs::DevScratch scratch_of(nqs_ham h) {
 // amplitude and 8 or 16 of bits per sample, against 64 or 96 of slots).
 void set_pairs(nqs::DevScratch *s, nqs_ham h, const nqs::EvalLaunch &L, char *slots, void *join) {
     s->pairs = L.pairs;
+    s->pairs_rule = L.pairs_rule;
     s->pairs_split = L.pairs_split;
     s->ppart = L.pairs_in_join ? static_cast<double *>(join) : s->part;
     if (L.pairs) nqs::pairs_scratch_layout(L.n, slots, s);
@@ -327,7 +328,7 @@ struct EvalKey {
     const void *slots, *shx, *part, *filter, *efilter, *small, *eblk, *jmem;
     uint32_t slot_cap;
     int energy, join_only;
-    int pairs, pairs_split, pairs_in_join;
+    int pairs, pairs_rule, pairs_split, pairs_in_join;
     const void *epart, *ehost;
 };
 static_assert(sizeof(EvalKey) <= sizeof(nqs_ham_s::eval_key), "key fits");
@@ -423,7 +424,8 @@ int eval_impl(nqs_ham h, int64_t n, const uint64_t *samples, const int64_t *weig
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool dump = hit_idx || sign_bits;
     nqs::EvalLaunch L = nqs::plan_eval(h->dt, n, dump, &h->tune);
-    // (only where a join is launched and may be chosen)
+    // (only where a join is launched and may be chosen; it decides by the
+    // rule of the full launch, L.pairs_rule)
     L.join_only = join_only && L.join && !dump ? 1 : 0;
     if (L.join_only) L.pairs = 0;
     int rc = ensure_scratch(h, n, plan_chunks(h, L), st, L.eparts_log2 > 0, plan_join_bytes(h, L));
@@ -468,6 +470,7 @@ int eval_impl(nqs_ham h, int64_t n, const uint64_t *samples, const int64_t *weig
         key.energy = energy ? 1 : 0;
         key.join_only = L.join_only;
         key.pairs = L.pairs;
+        key.pairs_rule = L.pairs_rule;
         key.pairs_split = L.pairs_split;
         key.pairs_in_join = L.pairs_in_join;
         key.epart = energy ? h->epart : nullptr;

@@ -237,6 +237,8 @@ struct DevScratch {
     // sample hash, which such a launch does not build), the shares the
     // samples y are split into (one partial each) and those partials
     int pairs;
+    int pairs_rule;             // 1: the join is weighed against the comparison of all pairs
+                                // (the alternative of the plan, whatever this launch holds of it)
     int pairs_split;
     double *ppart;              // [pairs_split][n][2] double-doubles (re, im); undivided [n][2]
     char *prec;
@@ -309,6 +311,9 @@ struct EvalLaunch {
     // comparison of all pairs of samples instead of the enumeration or
     // streaming (DevScratch::pairs), and the shares of its columns
     int pairs;
+    // whether the device weighs the join against that comparison: what is
+    // planned besides the join, also in a launch of the join's kernels alone
+    int pairs_rule;
     int pairs_split;
     int pairs_in_join;  // 1: its partials in the pair join's scratch
     // 1: the scratch holds the pair join's arrays (also where all pairs are

@@ -410,7 +410,7 @@ __device__ __forceinline__ void join_decide(const DevTable &tab, const DevScratc
     const double cost = (tiles ? 1.0 : 4.0) * cand + 40.0 * entries + 1.0e7;
     const bool fits = sc.jctl[kJoinCtlOver] == 0ull;
     bool chosen = fits && (sc.join_force != 0 || cost < alt);
-    if (sc.pairs == 2) {
+    if (sc.pairs_rule) {
         // beside the comparison of all pairs (0.09 ps a pair, 0.055 in wide
         // blocks, and 8 us) the
         // grouping is spent either way: what counts is the pair kernel, about

@@ -2688,11 +2688,13 @@ EvalLaunch plan_eval(const DevTable &tab, int64_t n, bool dump, const Tuning *tu
     }
     L.join_scratch = L.join;
     L.pairs = 0;
+    L.pairs_rule = 0;
     L.pairs_split = 1;
     L.pairs_in_join = 0;
     if (want == kStrategyAuto && pairs_cheaper(tab, n)) {
         L.pairs = L.join && n > kPairsDirect ? 2 : 1;
         if (L.pairs == 1) L.join = 0;
+        L.pairs_rule = L.join;
         // two shares of the columns, for shorter blocks, and up to four
         // until every compute unit has two (a share's partial takes the room
         // of two; the join's scratch is free where no join is launched):
