@@ -1055,7 +1055,8 @@ int nqs_eloc_energy(nqs_ham h, int64_t n, const uint64_t *samples, const int64_t
         std::atomic_thread_fence(std::memory_order_acquire);
         const unsigned chosen = *hchosen;
         h->join_likely = chosen == 1u;
-        if (!join_only || chosen == 1u) break;
+        // (2: no join was launched, so the launch was complete)
+        if (!join_only || chosen != 0u) break;
     }
     int err = h->host_err.exchange(0);
     if (err == 0) {

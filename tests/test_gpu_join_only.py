@@ -112,3 +112,20 @@ def test_a_joined_batch_is_evaluated_once(torch_dev):
     assert general.plan()["join_ran"] == 1
     assert evaluations(torch, lambda: step(torch, general, batch)) == 1
     general.close()
+
+
+def test_a_batch_below_the_grouping_is_evaluated_once(torch_dev):
+    """The step after a joined one that has no join to launch."""
+    torch = torch_dev
+    K = 20
+    h, eri = W.integrals(np.random.default_rng([31, K]), K, 4.0)
+    ham = nqs.Hamiltonian(*W.jw_terms(h, eri)[:3], 2 * K, W.spin_masks(2 * K))
+    large = inputs(torch, scored_samples(K, 10, 10, 9000, 0.0, 1), 1)
+    small = inputs(torch, scored_samples(K, 10, 10, 8192, 0.0, 4), 4)
+    step(torch, ham, large)
+    assert ham.plan()["join_ran"] == 1
+    say("evaluations: molecule, a joined batch and then one below the grouping")
+    assert evaluations(torch, lambda: step(torch, ham, large)) == 1
+    assert evaluations(torch, lambda: step(torch, ham, small)) == 1
+    assert ham.plan()["join_ran"] == -1
+    ham.close()
