@@ -149,8 +149,8 @@ nqs::DevScratch scratch_of(nqs_ham h) {
 }
 
 // The comparison of all pairs, its scratch in the space of the sample hash
-// (kMinSlots or 4 n slots hold it: a 32-byte record, 16 bytes of inverse
-// amplitude and 8 or 16 of bits per sample, against 64 or 96 of slots).
+// (kMinSlots or 4 n slots hold it: a 32-byte record and 8 or 16 bytes of bits
+// per sample, against 64 or 96 of slots).
 void set_pairs(nqs::DevScratch *s, nqs_ham h, const nqs::EvalLaunch &L, char *slots, void *join) {
     s->pairs = L.pairs;
     s->pairs_rule = L.pairs_rule;
@@ -343,7 +343,7 @@ hipError_t issue_eval(nqs_ham h, const nqs::DevScratch &sc, const nqs::EvalLaunc
     const bool prof = h->profiling && may_profile;
     if (prof && (e = hipEventRecord(h->ev[0], s)) != hipSuccess) return e;
     if ((e = nqs::launch_hash(h->dt, sc, sc.slot_mask + 1u, samples, weights, log_amp, phase, n,
-                              precision, hit_idx || sign_bits, s, prof ? h->ev[4] : nullptr, L.join_only != 0)) != hipSuccess)
+                              s, prof ? h->ev[4] : nullptr, L.join_only != 0)) != hipSuccess)
         return e;
     if (prof && (e = hipEventRecord(h->ev[1], s)) != hipSuccess) return e;
     const int64_t sign_words = (h->dt.n_terms + 31) / 32;

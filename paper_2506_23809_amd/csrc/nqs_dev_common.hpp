@@ -514,56 +514,23 @@ __device__ __forceinline__ AccF32 group_sum_f32(const DevTable &tab, int64_t g, 
     return a;
 }
 
-// psi(x') / psi(x) in FP64 is the product of psi(x') and 1 / psi(x), each
-// from its own sample (so that a kernel with many hits forms them once per
-// sample instead of an exponential, a sine and a cosine per hit; the pair
-// kernel's 37,843 gathered 40-qubit samples took 546 us with those and 489
-// without).  It is also nearer: the differences of logarithms and phases are
-// rounded before they are used (error of a ratio, rms against 64-bit
-// mantissas, phases over (0, 2 pi): 2.0e-16 and 1.2e-16 of its modulus for
-// log-amplitudes of N(0, 2), 3.1e-16 and 1.2e-16 where they fall to -15; of a
-// sum of 100, 5.1e-16 and 2.1e-16).  Outside |log-amplitude| < 300 a product
-// could overflow where the ratio does not: those amplitudes are NaN, and a
-// ratio that comes out NaN is taken from the differences.
-constexpr double kPsiRange = 300.0;
-
-__device__ __forceinline__ double2 psi_of(double la, double ph) {
-    double sn, cs;
-    sincos(ph, &sn, &cs);
-    const double m = fabs(la) < kPsiRange ? exp(la) : __builtin_nan("");
-    return make_double2(m * cs, m * sn);
-}
-
-__device__ __forceinline__ double2 psi_inverse(double la, double ph) {
-    const double2 r = psi_of(-la, ph);
-    return make_double2(r.x, -r.y);
-}
-
-__device__ __forceinline__ double2 psi_product(double2 y, double2 inv) {
-    return make_double2(fma(y.x, inv.x, -(y.y * inv.y)), fma(y.x, inv.y, y.y * inv.x));
-}
-
-// The ratio from the differences (out of line: hardly ever taken).
-[[maybe_unused]] static __device__ __noinline__ double2 ratio_of_differences(double da, double dphi) {
+// psi(x') / psi(x) in FP64 from the log-amplitude and phase differences (as
+// the product of psi(x') and 1 / psi(x), each formed once per sample, it took
+// the pair kernel a tenth less time, but was further off wherever the
+// differences are exact or small: log-amplitudes -8 +- 0.1 of one phase
+// 8.3e-17 rms instead of 4.9e-17, and no imaginary part was exactly 0).
+__device__ __forceinline__ double2 amp_ratio_inline(double da, double dphi) {
     double sn, cs;
     sincos(dphi, &sn, &cs);
     const double mag = exp(da);
     return make_double2(mag * cs, mag * sn);
 }
 
-// The ratio from the four numbers, for kernels with few hits.
-__device__ __forceinline__ double2 amp_ratio_inline(double lay, double phy, double lax,
-                                                    double phx) {
-    const double2 r = psi_product(psi_of(lay, phy), psi_inverse(lax, phx));
-    return r.x == r.x ? r : ratio_of_differences(lay - lax, phy - phx);
-}
-
 // Out of line: inlined into a kernel's partner or probe loop, the exp and
 // sincos constants stay in registers across the whole loop and cost it
 // waves per SIMD (the call is made only on a hit).
-[[maybe_unused]] static __device__ __noinline__ double2 amp_ratio_f64(double lay, double phy, double lax,
-                                                     double phx) {
-    return amp_ratio_inline(lay, phy, lax, phx);
+[[maybe_unused]] static __device__ __noinline__ double2 amp_ratio_f64(double da, double dphi) {
+    return amp_ratio_inline(da, dphi);
 }
 
 // psi(x') / psi(x) in FP32 from the FP64 log-psi difference; the phase

@@ -233,16 +233,15 @@ struct DevScratch {
     int join_cap;               // entries of a partition's region
     int join_force;             // 1: join whenever it can run, 0: when cheaper
     // comparison of all pairs: 0 none, 1 for this launch, 2 unless the device
-    // chose the pair join; its records, inverse amplitudes and bits (in the space of the
-    // sample hash, which such a launch does not build), the shares the
-    // samples y are split into (one partial each) and those partials
+    // chose the pair join; its records and bits (in the space of the sample
+    // hash, which such a launch does not build), the shares the samples y
+    // are split into (one partial each) and those partials
     int pairs;
     int pairs_rule;             // 1: the join is weighed against the comparison of all pairs
                                 // (the alternative of the plan, whatever this launch holds of it)
     int pairs_split;
     double *ppart;              // [pairs_split][n][2] double-doubles (re, im); undivided [n][2]
     char *prec;
-    char *pinv;
     char *pkey;
 };
 
@@ -356,10 +355,10 @@ constexpr int64_t kPairsWide = 32768;
 void pairs_scratch_layout(int64_t n, char *base, DevScratch *sc);
 hipError_t launch_pairs_prep(const DevTable &tab, const DevScratch &sc, const uint64_t *samples,
                              const int64_t *weights, const double *log_amp, const double *phase,
-                             int64_t n, int precision, bool dump, hipStream_t st);
-hipError_t launch_pairs(const DevTable &tab, const DevScratch &sc, const double *log_amp,
-                        const double *phase, int64_t n, int precision, int32_t *hit_idx,
-                        uint32_t *sign_bits, int64_t sign_words, hipStream_t st);
+                             int64_t n, hipStream_t st);
+hipError_t launch_pairs(const DevTable &tab, const DevScratch &sc, int64_t n, int precision,
+                        int32_t *hit_idx, uint32_t *sign_bits, int64_t sign_words,
+                        hipStream_t st);
 
 constexpr int kStrategyAuto = 0, kStrategyStream = 1, kStrategyEnum = 2, kStrategyJoin = 3;
 
@@ -386,7 +385,7 @@ EvalLaunch plan_eval(const DevTable &tab, int64_t n, bool dump, const Tuning *tu
 // neither cleared nor filled: nothing reads it.
 hipError_t launch_hash(const DevTable &tab, const DevScratch &sc, uint32_t capacity,
                        const uint64_t *samples, const int64_t *weights, const double *log_amp,
-                       const double *phase, int64_t n, int precision, bool dump, hipStream_t st,
+                       const double *phase, int64_t n, hipStream_t st,
                        hipEvent_t after_grouping = nullptr,
                        bool join_only = false);
 // Eq. 1 taken beside an evaluation: the finish kernel writes one partial set

@@ -510,7 +510,7 @@ __device__ __forceinline__ bool join_hit(const DevTable &tab, const Key<W> &x, c
         } else {
             hsum = group_sum<W, DUMP>(tab, g, x, row, terms, cnt);
         }
-        const double2 rat = amp_ratio_f64(log_amp[j], phase[j], la, ph);
+        const double2 rat = amp_ratio_f64(log_amp[j] - la, phase[j] - ph);
         re = hsum * rat.x;
         im = hsum * rat.y;
     } else {

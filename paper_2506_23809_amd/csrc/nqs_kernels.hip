@@ -199,7 +199,7 @@ __device__ __forceinline__ void lookup_item(
                     } else {
                         hsum = group_sum<W, DUMP>(tab, g, xl, row, &n_terms);
                     }
-                    const double2 rat = amp_ratio_f64(log_amp[j], phase[j], lal, phl);
+                    const double2 rat = amp_ratio_f64(log_amp[j] - lal, phase[j] - phl);
                     cre = hsum * rat.x;
                     cim = hsum * rat.y;
                 } else {
@@ -595,8 +595,9 @@ __device__ __forceinline__ void enum_candidate(
         } else {
             hsum = group_sum<W, DUMP>(tab, g, x, row, &cnt.terms, terms);
         }
-        // (inline: this kernel's occupancy is set by its LDS)
-        const double2 rat = amp_ratio_inline(log_amp[j], phase[j], la, ph);
+        // (inline: this kernel's occupancy is set by its LDS, and a call
+        // would only add a stack)
+        const double2 rat = amp_ratio_inline(log_amp[j] - la, phase[j] - ph);
         c.re = hsum * rat.x;
         c.im = hsum * rat.y;
     } else {
@@ -2414,7 +2415,7 @@ hipError_t launch_batch(const JobDesc *d_jobs, int n_jobs, const WorkItem *d_ite
         if (J.n == 0) continue;
         if (J.sc.pairs) {
             const hipError_t e = launch_pairs_prep(J.tab, J.sc, J.samples, J.weights, J.log_amp,
-                                                   J.phase, J.n, precision, false, st);
+                                                   J.phase, J.n, st);
             if (e != hipSuccess) return e;
         }
         if (!J.sc.jctl) continue;
@@ -2453,8 +2454,7 @@ hipError_t launch_batch(const JobDesc *d_jobs, int n_jobs, const WorkItem *d_ite
         if (J.n == 0) continue;
         const int pr = (J.kind & kJobIntegrals) ? NQS_FP64 : precision;
         if (J.sc.pairs) {
-            const hipError_t e = launch_pairs(J.tab, J.sc, J.log_amp, J.phase, J.n, pr, nullptr,
-                                              nullptr, 0, st);
+            const hipError_t e = launch_pairs(J.tab, J.sc, J.n, pr, nullptr, nullptr, 0, st);
             if (e != hipSuccess) return e;
         }
         if (!J.sc.jctl) continue;
@@ -2727,13 +2727,12 @@ EvalLaunch plan_eval(const DevTable &tab, int64_t n, bool dump, const Tuning *tu
 
 hipError_t launch_hash(const DevTable &tab, const DevScratch &sc, uint32_t capacity,
                        const uint64_t *samples, const int64_t *weights, const double *log_amp,
-                       const double *phase, int64_t n, int precision, bool dump, hipStream_t st,
-                       hipEvent_t after_grouping, bool join_only) {
+                       const double *phase, int64_t n, hipStream_t st, hipEvent_t after_grouping,
+                       bool join_only) {
     if (sc.pairs) {
         // all pairs are compared (unless the join's decision is to run): no
         // sample hash
-        hipError_t e = launch_pairs_prep(tab, sc, samples, weights, log_amp, phase, n, precision, dump,
-                                         st);
+        hipError_t e = launch_pairs_prep(tab, sc, samples, weights, log_amp, phase, n, st);
         if (e == hipSuccess && sc.jctl)
             e = launch_join_prep(tab, sc, samples, weights, n,
                                  tab.n_groups - (tab.has_diagonal ? 1 : 0), false, st);
@@ -2873,7 +2872,7 @@ hipError_t launch_eloc(const DevTable &tab, const DevScratch &sc, const EvalLaun
             hipLaunchKernelGGL(fill_i32_kernel, dim3(static_cast<unsigned>((cnt + 255) / 256)),
                                dim3(256), 0, st, hit_idx, cnt, -1);
         }
-        e = launch_pairs(tab, sc, log_amp, phase, n, precision, hit_idx, sign_bits, sign_words, st);
+        e = launch_pairs(tab, sc, n, precision, hit_idx, sign_bits, sign_words, st);
         if (e != hipSuccess) return e;
     }
     if (en && !L.join_only && !sc.pairs) {

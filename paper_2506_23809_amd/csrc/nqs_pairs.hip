@@ -41,26 +41,19 @@ constexpr int kPairsQueue = 128;  // entries per queue and wave (64 are taken at
 // single excitations 2 n_qubits - 2 and an occupation row).
 constexpr uint32_t kShortTerms = 12;
 
-// A sample: its bits and, in FP64, its amplitude (the row's: its inverse), in
-// FP32 its log-amplitude and phase.
+// A sample: its bits, log-amplitude and phase.
 struct alignas(16) PairRec {
     uint64_t w0, w1;
-    double a, b;
+    double la, ph;
 };
-
-inline bool pairs_f32(const DevTable &tab, int precision, bool dump) {
-    return precision == NQS_FP32_KAHAN && !dump && !tab.sc;
-}
 
 // Clears the counters and control words of the launch, makes the sample
 // checks of the hash build, and lays out the samples for the pair kernel:
-// one 32-byte record each, in FP64 the inverse amplitudes, and the bits by
-// tiles (4.1 us for 4,096 samples, 0.5 of them the amplitudes).
+// one 32-byte record each and the bits by tiles (3.6 us for 4,096 samples).
 __global__ __launch_bounds__(256) void pairs_prep_kernel(
     DevTable tab, DevScratch sc, const uint64_t *__restrict__ samples,
     const int64_t *__restrict__ weights, const double *__restrict__ log_amp,
-    const double *__restrict__ phase, int64_t n, bool f32, uint32_t jparts,
-    uint32_t jhit_words) {
+    const double *__restrict__ phase, int64_t n, uint32_t jparts, uint32_t jhit_words) {
     const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s < static_cast<uint32_t>(kCounters * kCounterSlots)) sc.counters[s] = 0;
     if (s == 0) *sc.mixed = 0;
@@ -84,14 +77,7 @@ __global__ __launch_bounds__(256) void pairs_prep_kernel(
         const uint64_t w0 = samples[2 * i], w1 = samples[2 * i + 1];
         const bool bad = nq >= 64 ? ((w1 >> (nq - 64)) != 0) : ((w0 >> nq) != 0 || w1 != 0);
         if (bad || (weights && weights[i] < 0)) latch(sc.err, NQS_E_RANGE);
-        PairRec r{w0, w1, log_amp[i], phase[i]};
-        if (!f32) {
-            const double2 psi = psi_of(r.a, r.b);
-            r.a = psi.x;
-            r.b = psi.y;
-            reinterpret_cast<double2 *>(sc.pinv)[i] = psi_inverse(log_amp[i], phase[i]);
-        }
-        reinterpret_cast<PairRec *>(sc.prec)[i] = r;
+        reinterpret_cast<PairRec *>(sc.prec)[i] = PairRec{w0, w1, log_amp[i], phase[i]};
     }
 }
 
@@ -124,8 +110,7 @@ struct PairsWave {
 // instead of 508 for 20,001 gathered samples, at 96 it spilled (600).
 template <int W, int H, bool DUMP, int P, bool SCV>
 __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
-    DevTable tab, DevScratch sc, int64_t n, const double *__restrict__ log_amp,
-    const double *__restrict__ phase, int32_t *__restrict__ hit_idx,
+    DevTable tab, DevScratch sc, int64_t n, int32_t *__restrict__ hit_idx,
     uint32_t *__restrict__ sign_bits, int64_t sign_words) {
     if (!pairs_chosen(sc)) return;
     constexpr int R = 32 * H;  // samples x of the block
@@ -141,14 +126,8 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
         const int64_t at = i < n ? i : n - 1;
         xs[threadIdx.x].w0 = rec[at].w0;
         xs[threadIdx.x].w1 = rec[at].w1;
-        if constexpr (P == NQS_FP64) {
-            const double2 inv = reinterpret_cast<const double2 *>(sc.pinv)[at];
-            xs[threadIdx.x].a = inv.x;
-            xs[threadIdx.x].b = inv.y;
-        } else {
-            xs[threadIdx.x].a = rec[at].a;
-            xs[threadIdx.x].b = rec[at].b;
-        }
+        xs[threadIdx.x].la = rec[at].la;
+        xs[threadIdx.x].ph = rec[at].ph;
     }
     __syncthreads();
     PairsWave &me = waves[wave];
@@ -181,8 +160,8 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     };
     // <x|H|y> psi(y) / psi(x) of a pair whose group is g
-    auto evaluate = [&](const PairRec &x, const PairRec &y, int64_t i, int64_t j, int64_t g,
-                        uint32_t cnt, double &re, double &im) {
+    auto evaluate = [&](const PairRec &x, const PairRec &y, int64_t i, int64_t g, uint32_t cnt,
+                        double &re, double &im) {
         const Key<W> xk = rec_key<W>(x);
         if constexpr (P == NQS_FP64) {
             double h;
@@ -192,15 +171,13 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
                 uint32_t *row = (DUMP && sign_bits) ? sign_bits + i * sign_words : nullptr;
                 h = group_sum<W, DUMP>(tab, g, xk, row, &n_term, cnt);
             }
-            double2 rat = psi_product(make_double2(y.a, y.b), make_double2(x.a, x.b));
-            if (rat.x != rat.x)
-                rat = ratio_of_differences(log_amp[j] - log_amp[i], phase[j] - phase[i]);
+            const double2 rat = amp_ratio_f64(y.la - x.la, y.ph - x.ph);
             re = h * rat.x;
             im = h * rat.y;
         } else {
             const AccF32 h = group_sum_f32<W>(tab, g, xk, &n_term, cnt);
             float rr, ri;
-            ratio_f32(y.a - x.a, y.b - x.b, rr, ri);
+            ratio_f32(y.la - x.la, y.ph - x.ph, rr, ri);
             const float pre = h.s * rr, pim = h.s * ri;
             re = static_cast<double>(pre) + static_cast<double>(fmaf(h.s, rr, -pre) + h.c * rr);
             im = static_cast<double>(pim) + static_cast<double>(fmaf(h.s, ri, -pim) + h.c * ri);
@@ -215,7 +192,7 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
         if (on) {
             const uint2 e = me.lq[lane];
             x = e.x & 63u;
-            evaluate(xs[x], rec[e.x >> 6], x0 + x, e.x >> 6, e.y, 0u, re, im);
+            evaluate(xs[x], rec[e.x >> 6], x0 + x, e.y, 0u, re, im);
         }
         deposit(on, x, re, im);
     };
@@ -263,7 +240,7 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
                         ++n_hit;
                         later = SCV ? pop == 2 : cnt > kShortTerms;
                         now = !later;
-                        if (now) evaluate(xs[x], y, i, j, g, cnt, re, im);
+                        if (now) evaluate(xs[x], y, i, g, cnt, re, im);
                     }
                 }
             }
@@ -418,17 +395,16 @@ __global__ __launch_bounds__(kPairsThreads, 4) void pairs_kernel(
 
 }  // namespace
 
-// 32 + 16 + 8 or 16 bytes per sample, the last for whole tiles: within the
+// 32 + 8 or 16 bytes per sample, the latter for whole tiles: within the
 // hash's 64 or 96 (128 slots at least).
 void pairs_scratch_layout(int64_t n, char *base, DevScratch *sc) {
     sc->prec = base;
-    sc->pinv = base + sizeof(PairRec) * n;
-    sc->pkey = sc->pinv + sizeof(double2) * n;
+    sc->pkey = base + sizeof(PairRec) * n;
 }
 
 hipError_t launch_pairs_prep(const DevTable &tab, const DevScratch &sc, const uint64_t *samples,
                              const int64_t *weights, const double *log_amp, const double *phase,
-                             int64_t n, int precision, bool dump, hipStream_t st) {
+                             int64_t n, hipStream_t st) {
     const uint32_t jparts = sc.jctl ? static_cast<uint32_t>(sc.join_parts) : 0u;
     const uint32_t jhw =
         sc.jctl ? static_cast<uint32_t>((tab.join_blocks * n + 31) / 32) : 0u;
@@ -437,15 +413,15 @@ hipError_t launch_pairs_prep(const DevTable &tab, const DevScratch &sc, const ui
     for (int64_t v : least) span = v > span ? v : span;
     hipLaunchKernelGGL(pairs_prep_kernel, dim3(static_cast<unsigned>((span + 255) / 256)),
                        dim3(256), 0, st, tab, sc, samples, weights, log_amp, phase, n,
-                       pairs_f32(tab, precision, dump), jparts, jhw);
+                       jparts, jhw);
     return hipGetLastError();
 }
 
-hipError_t launch_pairs(const DevTable &tab, const DevScratch &sc, const double *log_amp,
-                        const double *phase, int64_t n, int precision, int32_t *hit_idx,
-                        uint32_t *sign_bits, int64_t sign_words, hipStream_t st) {
+hipError_t launch_pairs(const DevTable &tab, const DevScratch &sc, int64_t n, int precision,
+                        int32_t *hit_idx, uint32_t *sign_bits, int64_t sign_words,
+                        hipStream_t st) {
     const bool dump = hit_idx || sign_bits;
-    const bool f32 = pairs_f32(tab, precision, dump);
+    const bool f32 = precision == NQS_FP32_KAHAN && !dump && !tab.sc;
     const bool wide = n > kPairsWide;
     const int64_t rows = wide ? 64 : 32;
     const dim3 grid(static_cast<unsigned>((n + rows - 1) / rows),
@@ -454,10 +430,10 @@ hipError_t launch_pairs(const DevTable &tab, const DevScratch &sc, const double 
     do {                                                                                        \
         if (wide)                                                                               \
             hipLaunchKernelGGL((pairs_kernel<Wd, 2, D, Pr, SCI>), grid, dim3(kPairsThreads), 0, \
-                               st, tab, sc, n, log_amp, phase, hit_idx, sign_bits, sign_words); \
+                               st, tab, sc, n, hit_idx, sign_bits, sign_words); \
         else                                                                                    \
             hipLaunchKernelGGL((pairs_kernel<Wd, 1, D, Pr, SCI>), grid, dim3(kPairsThreads), 0, \
-                               st, tab, sc, n, log_amp, phase, hit_idx, sign_bits, sign_words); \
+                               st, tab, sc, n, hit_idx, sign_bits, sign_words); \
     } while (0)
     const bool w1 = tab.n_qubits <= 63;
     if (tab.sc) {

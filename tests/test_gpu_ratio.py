@@ -66,3 +66,20 @@ def test_zero_amplitude_and_nan_phase(problem, strategy):
     e, _, _ = run(torch, ham, S, la, ph2, strategy=strategy)
     assert reached.any() and np.array_equal(np.isnan(e[keep].real), reached)
     assert (np.abs(e[keep] - alone)[~reached] <= TOL["fp64"] * ab[~reached]).all()
+
+
+@pytest.mark.parametrize("strategy", ["auto", "join", "enum", "stream"])
+def test_equal_amplitudes_and_phases_leave_no_trace(problem, strategy):
+    """Where all samples have one log-amplitude and one phase, every ratio is
+    exactly 1: the bits of an amplitude of 1, and no imaginary part.  With one
+    phase and different log-amplitudes there is none either."""
+    torch, ham, _, S, la, _ = problem
+    say(f"ratio: equal amplitudes and phases, {strategy}")
+    zero = np.zeros(N)
+    one, _, _ = run(torch, ham, S, zero, zero, strategy=strategy)
+    for amp, phase in ((-7.3, 0.0), (0.1, 0.7), (-280.0, 2.9), (500.0, -1.3)):
+        e, _, _ = run(torch, ham, S, zero + amp, zero + phase, strategy=strategy)
+        assert np.array_equal(e.view(np.uint64), one.view(np.uint64))
+    for phase in (0.7, math.pi):
+        e, _, _ = run(torch, ham, S, la, zero + phase, strategy=strategy)
+        assert (e.imag == 0.0).all()
