@@ -806,6 +806,7 @@ int create_handle(nqs_ham *out, const nqs::HostTable &T, const std::vector<doubl
     d.diag_q8 = T.diag_occ ? reinterpret_cast<const int8_t *>(base + pieces[15].off) : nullptr;
     d.diag_scale = diag_scale;
     d.diag_jtiles = diag_jtiles;
+    if (h1) nqs::diag_tile_qubits(T, d.diag_tile);
     *out = h;
     return NQS_OK;
 }
@@ -880,13 +881,16 @@ int nqs_ham_create_integrals(nqs_ham *out, int n_orbitals, const double *h1e, co
         // of them the Coulomb integral, less the exchange one for equal spins
         const int nq = 2 * K;
         T.diag.assign(1 + nq + size_t(nq) * (nq - 1) / 2, 0.0);
+        T.diag_exact = true;
         for (int j = 0; j < nq; ++j) {
             const int b = j >> 1;
             T.diag[1 + j] = h1[size_t(b) * K + b];
             for (int i = 0; i < j; ++i) {
                 const int a = i >> 1;
-                T.diag[1 + nq + size_t(j) * (j - 1) / 2 + i] =
-                    E(a, a, b, b) - ((i & 1) == (j & 1) ? E(a, b, b, a) : 0.0);
+                const double J = E(a, a, b, b), X = (i & 1) == (j & 1) ? E(a, b, b, a) : 0.0;
+                const double v = J - X;
+                T.diag[1 + nq + size_t(j) * (j - 1) / 2 + i] = v;
+                T.diag_exact = T.diag_exact && static_cast<long double>(J) - X == v;
             }
         }
         T.diag_occ = true;

@@ -471,6 +471,14 @@ __device__ __forceinline__ double sc_diagonal(const DevTable &tab, const Key<W> 
     return d;
 }
 
+// Whether the digit tiles give the sample's diagonal as closely as its sum.
+template <int W>
+__device__ __forceinline__ bool sc_diagonal_tiled(const DevTable &tab, const Key<W> &x) {
+    uint64_t v = x.w[0] & tab.diag_tile[0];
+    if constexpr (W == 2) v |= x.w[W - 1] & tab.diag_tile[1];
+    return v != 0ull;
+}
+
 // ---- FP32 form with compensation (precision NQS_FP32_KAHAN)
 //
 // A group's sum enters as an FP32 pair hi + lo (of its FP64 value); the terms

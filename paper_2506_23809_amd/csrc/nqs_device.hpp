@@ -68,6 +68,7 @@ struct DevTable {
     const int8_t *diag_q8;
     double diag_scale;
     int diag_jtiles;
+    uint64_t diag_tile[2];  // integral form: the tiles serve samples that occupy one of these
     // pair join: the qubits split into join_blocks disjoint blocks (jmask);
     // two bit strings at Hamming distance at most max_flip < join_blocks
     // agree on at least one block (pigeonhole), so every connected pair of

@@ -2133,7 +2133,7 @@ constexpr int kFinishMfmaThreads = 1024;
 constexpr int kFinishAlone = 512;
 constexpr int kDiagMaxTiles = diag_mfma_tiles(8);
 
-template <int W, int P>
+template <int W, int P, bool SCV>
 __global__ __launch_bounds__(kFinishMfmaThreads) void eloc_finish_mfma_kernel(
     DevTable tab, DevScratch sc, const uint64_t *__restrict__ samples, int64_t n,
     int64_t n_chunks, int enum_on, double *__restrict__ eloc, EnergyFused ef, bool alone) {
@@ -2150,7 +2150,9 @@ __global__ __launch_bounds__(kFinishMfmaThreads) void eloc_finish_mfma_kernel(
     const diag_v4i *src = reinterpret_cast<const diag_v4i *>(tab.diag_q8);
     for (int k = threadIdx.x; k < words; k += blockDim.x) tiles[k] = src[k];
     __syncthreads();
-    const double d = diag_occ_mfma<W>(tab, x, tiles);
+    double d = diag_occ_mfma<W>(tab, x, tiles);
+    if constexpr (SCV)
+        if (!sc_diagonal_tiled<W>(tab, x)) d = sc_diagonal<W>(tab, x);
     // the index again (two registers not held across the diagonal)
     unsigned tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
@@ -2333,7 +2335,8 @@ __global__ __launch_bounds__(256) void batch_finish_kernel(const JobDesc *__rest
         if ((J.kind & 1) == 0) {
             Key<1> x;
             x.w[0] = i < J.n ? J.samples[2 * i] : 0ull;
-            const double d = diag_occ_mfma<1>(J.tab, x, tiles);
+            double d = diag_occ_mfma<1>(J.tab, x, tiles);
+            if (J.tab.sc && !sc_diagonal_tiled<1>(J.tab, x)) d = sc_diagonal<1>(J.tab, x);
             finish_one<1, false, P, false>(J.tab, J.sc, J.samples, J.n, chunks, en, J.eloc,
                                            nullptr, nullptr, 0, i, nullptr, nullptr, 0, nullptr,
                                            nullptr, true, d);
@@ -2341,7 +2344,8 @@ __global__ __launch_bounds__(256) void batch_finish_kernel(const JobDesc *__rest
             Key<2> x;
             x.w[0] = i < J.n ? J.samples[2 * i] : 0ull;
             x.w[1] = i < J.n ? J.samples[2 * i + 1] : 0ull;
-            const double d = diag_occ_mfma<2>(J.tab, x, tiles);
+            double d = diag_occ_mfma<2>(J.tab, x, tiles);
+            if (J.tab.sc && !sc_diagonal_tiled<2>(J.tab, x)) d = sc_diagonal<2>(J.tab, x);
             finish_one<2, false, P, false>(J.tab, J.sc, J.samples, J.n, chunks, en, J.eloc,
                                            nullptr, nullptr, 0, i, nullptr, nullptr, 0, nullptr,
                                            nullptr, true, d);
@@ -2968,21 +2972,19 @@ hipError_t launch_eloc(const DevTable &tab, const DevScratch &sc, const EvalLaun
                             : (alone ? static_cast<int>((n + 63) / 64 * 64) : 256);
         const dim3 mgrid(static_cast<unsigned>((n + mth - 1) / mth));
         const dim3 mblk(mth);
+#define NQS_FINISH_MFMA(Wd, Pr, SCI)                                                          \
+    hipLaunchKernelGGL((eloc_finish_mfma_kernel<Wd, Pr, SCI>), mgrid, mblk, 0, st, tab, sc, samples, \
+                       n, chunks, fb, eloc, ef, alone)
         if (words == 1) {
-            if (f32)
-                hipLaunchKernelGGL((eloc_finish_mfma_kernel<1, NQS_FP32_KAHAN>), mgrid, mblk, 0,
-                                   st, tab, sc, samples, n, chunks, fb, eloc, ef, alone);
-            else
-                hipLaunchKernelGGL((eloc_finish_mfma_kernel<1, NQS_FP64>), mgrid, mblk, 0, st, tab,
-                                   sc, samples, n, chunks, fb, eloc, ef, alone);
+            if (tab.sc) NQS_FINISH_MFMA(1, NQS_FP64, true);
+            else if (f32) NQS_FINISH_MFMA(1, NQS_FP32_KAHAN, false);
+            else NQS_FINISH_MFMA(1, NQS_FP64, false);
         } else {
-            if (f32)
-                hipLaunchKernelGGL((eloc_finish_mfma_kernel<2, NQS_FP32_KAHAN>), mgrid, mblk, 0,
-                                   st, tab, sc, samples, n, chunks, fb, eloc, ef, alone);
-            else
-                hipLaunchKernelGGL((eloc_finish_mfma_kernel<2, NQS_FP64>), mgrid, mblk, 0, st, tab,
-                                   sc, samples, n, chunks, fb, eloc, ef, alone);
+            if (tab.sc) NQS_FINISH_MFMA(2, NQS_FP64, true);
+            else if (f32) NQS_FINISH_MFMA(2, NQS_FP32_KAHAN, false);
+            else NQS_FINISH_MFMA(2, NQS_FP64, false);
         }
+#undef NQS_FINISH_MFMA
         if (ev.after_finish && (e = hipEventRecord(ev.after_finish, st)) != hipSuccess) return e;
         if (ef.part && !alone)
             hipLaunchKernelGGL(energy_combine_kernel, dim3(1), dim3(kRedThreads), 0, st, ef.part,

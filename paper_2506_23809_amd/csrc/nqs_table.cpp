@@ -375,6 +375,23 @@ void build_diag_tiles(const HostTable &T, std::vector<int8_t> *out, double *scal
     }
 }
 
+void diag_tile_qubits(const HostTable &T, uint64_t out[2]) {
+    out[0] = out[1] = 0;
+    const int nq = T.n_qubits;
+    double top = 0.0;
+    for (size_t k = 1; k < T.diag.size(); ++k) top = std::max(top, std::fabs(T.diag[k]));
+    int e = 0;
+    std::frexp(top, &e);  // top < 2^e, as for the grid
+    bool exact = T.diag_exact;
+    for (size_t k = 1; exact && k < T.diag.size(); ++k) {
+        const double q = std::ldexp(T.diag[k], kDiagBits - e);
+        exact = q == std::nearbyint(q);
+    }
+    for (int q = 0; q < nq; ++q)
+        if (exact || std::fabs(T.diag[1 + q]) >= std::ldexp(1.0, e - 4))
+            out[q >> 6] |= 1ull << (q & 63);
+}
+
 void build_group_records(const HostTable &T, GroupRecords *out) {
     const int W = T.words, nq = T.n_qubits;
     out->rec.assign(static_cast<size_t>(T.n_groups) * kGroupWords, 0);

@@ -75,6 +75,7 @@ struct HostTable {
     //   <x|H_diag|x> = d[0] + sum_{j occ} (d[1 + j] + sum_{i occ, i < j} d[1 + nq + j (j - 1) / 2 + i])
     bool diag_occ = false;
     std::vector<double> diag;
+    bool diag_exact = false;  // integral form: no difference J - K in diag was rounded
 };
 
 // Fill max_flip, enum_ok, the spin qubit lists and the group index.
@@ -102,6 +103,15 @@ constexpr int kDiagDigits = 4;
 constexpr int kDiagLimbs = 2 * kDiagDigits;  // byte planes
 constexpr int kDiagBits = 59;
 void build_diag_tiles(const HostTable &T, std::vector<int8_t> *out, double *scale);
+// The integral form's diagonal is a sum over occupied orbitals alone, so a
+// large coefficient of an empty one must not coarsen it: the grid holds every
+// coefficient to 2^-59 of the largest one, an FP64 sum each sample's own.
+// Samples that occupy one of the qubits out[2] take the tiles: those with
+// |h_ii| of at least 2^-4 of the grid's range, at which the FP64 sum rounds as
+// coarsely (rms error of the tiles over that of the sum, random and decaying
+// integrals of 6 to 20 orbitals, 2 to 20 electrons: 0.07 to 1.00 from 2^-4 up,
+// 1.2 at 2^-5, 6.6 at 2^-8); all qubits where every coefficient is on the grid.
+void diag_tile_qubits(const HostTable &T, uint64_t out[2]);
 
 // The groups as the kernels read them: one 64-byte record per group (W mask
 // words, eight 64-bit words in all),
