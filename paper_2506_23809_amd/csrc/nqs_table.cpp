@@ -398,6 +398,10 @@ void build_group_records(const HostTable &T, GroupRecords *out) {
     out->codes.assign(static_cast<size_t>(T.n_terms), 0);
     out->z.clear();
     out->rows.clear();
+    // groups with a row, and the squared partial sums of all rows (by variant)
+    // and of their terms, for random occupations
+    std::vector<int64_t> with_row;
+    double row_sq[2] = {0.0, 0.0}, term_sq = 0.0;
     // odd[c & p] for four-bit c, p: parity by table (the host build has no
     // popcount instruction)
     static const uint8_t odd[16] = {0, 1, 1, 0, 1, 0, 0, 1, 1, 0, 0, 1, 0, 1, 1, 0};
@@ -464,10 +468,33 @@ void build_group_records(const HostTable &T, GroupRecords *out) {
                 if (at >= 0) r[1 + at] -= 2.0L * c;
             }
         }
+        for (const long double v : row) form = form && std::isfinite(static_cast<double>(v));
         if (!form) continue;
         for (int q = 0; q < W; ++q) rec[W + q] = base[q];
         value[2] = 1 + out->rows.size() / (2 * static_cast<size_t>(nq + 2));
         for (const long double v : row) out->rows.push_back(static_cast<double>(v));
+        with_row.push_back(g);
+        double sq = 0.0;
+        for (int64_t t = t0; t < t1; ++t) term_sq += sq += T.tc[t] * T.tc[t];
+        for (int b = 0; b < 2; ++b) {
+            const long double *r = &row[static_cast<size_t>(b) * (nq + 2)];
+            double mean = static_cast<double>(r[0]), var = 0.0;
+            for (int q = 0; q < nq; ++q) {
+                const double v = 0.5 * static_cast<double>(r[1 + q]);
+                mean += v;
+                var += v * v;
+                row_sq[b] += 0.5 * (mean * mean + var);
+            }
+        }
+    }
+    // an addition's rounding error goes with its sum: rows only where their
+    // partial sums are no larger than the terms' (written so that an overflow
+    // of either keeps the terms)
+    if (row_sq[0] <= term_sq && row_sq[1] <= term_sq) return;
+    out->rows.clear();
+    for (const int64_t g : with_row) {
+        uint64_t *rec = &out->rec[static_cast<size_t>(g) * kGroupWords];
+        rec[W] = rec[2 * W - 1] = rec[2 * W + 2] = 0;
     }
 }
 

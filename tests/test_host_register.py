@@ -179,6 +179,11 @@ static void run(int nq, int flips) {
     };
     for (int q = 0; q < nq; ++q)
         if (q % 3 || q >= 3 * flips) term(q < 64 ? 1ull << q : 0, q < 64 ? 0 : 1ull << (q - 64));
+    // (the string of the base balances them: the row form is kept)
+    double sum = 0.0;
+    for (const double v : c) sum += v;
+    term(0, 0);
+    c.back() = -sum;
     HostTable T;
     std::string err;
     if (build_table(nq, static_cast<int64_t>(c.size()), x.data(), z.data(), c.data(), nullptr, &T, &err)) {
