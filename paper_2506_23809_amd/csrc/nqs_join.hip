@@ -681,6 +681,7 @@ __global__ __launch_bounds__(kJoinPairThreads) void join_pair_kernel(
 
 // Shared state of one wave of the tile kernel: its 64 rows (entries) and
 // the queue of near pairs.
+static_assert(kJoinMaxBlocks * kJoinMaxSamples <= int64_t(1) << 26, "an entry fits a queue word");
 struct TileWave {
     uint64_t key[64];
     double con[2][64];           // contributions of a batch (re, im)

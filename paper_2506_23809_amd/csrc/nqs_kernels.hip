@@ -2616,7 +2616,7 @@ constexpr int64_t kPairsDirect = 8192;
 // qubits, 10,007 samples, 500 groups 195 and 157, 20,000 205 and 305; 26
 // qubits, 10,007 samples, 20,000 groups 540 and 399.
 bool pairs_cheaper(const DevTable &tab, int64_t n) {
-    // (the pair kernel packs a sample's index in 27 bits)
+    // (the pair kernel packs a sample's index in 26 bits)
     if (n > kJoinMaxSamples) return false;
     const double dn = static_cast<double>(n);
     const double pair = n > kPairsWide ? 0.055 : 0.09, groups = static_cast<double>(tab.n_groups);

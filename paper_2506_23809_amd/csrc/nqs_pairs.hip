@@ -40,6 +40,8 @@ constexpr int kPairsQueue = 128;  // entries per queue and wave (64 are taken at
 // double excitations of a molecule have 4 or 6 terms in one record, its
 // single excitations 2 n_qubits - 2 and an occupation row).
 constexpr uint32_t kShortTerms = 12;
+// A queue entry is a sample's index above the six bits of its row.
+static_assert(kJoinMaxSamples <= int64_t(1) << 26, "a sample's index fits a queue entry");
 
 // A sample: its bits, log-amplitude and phase.
 struct alignas(16) PairRec {
