@@ -385,8 +385,8 @@ int nqs_debug_dump(nqs_ham h, int64_t n, const uint64_t *samples, const double *
  *     split by a content fingerprint), and only pairs of samples sharing a
  *     group are tested (Hamming distance, then the group index).  Its cost
  *     is the sum of squared group sizes, independent of the table's size:
- *     for samples spread over a large sector it is far below both others.  Needs m + 1 <= 8, at most 2^21 samples, and at
- *     most 8192 entries in one partition of 2^11 buckets (a hash range of
+ *     for samples spread over a large sector it is far below both others.
+ *     Needs m + 1 <= 8, at most 2^21 samples, and at most 8192 entries in one partition of 2^11 buckets (a hash range of
  *     the bucket keys; about two thousand entries each on average);
  *     otherwise (decided on the device) the enumeration or streaming
  *     strategy runs instead.
@@ -496,8 +496,11 @@ int nqs_batch_destroy(nqs_batch b);
  * A dispatcher thread admits pending requests in arrival order into free
  * lanes, as long as the resident data plus the footprint of every request
  * on the device stays within hbm_budget_bytes, and launches each on its
- * lane with the plan nqs_eloc_eval would take (the device picks the pair
- * join, the enumeration or streaming).  Lanes run concurrently, so requests
+ * lane with the plan nqs_eloc_eval would take (all pairs, the pair join, the
+ * enumeration or streaming).  While requests run, it polls their completion
+ * and keeps one host core busy, for up to 1 ms after each admission or
+ * completion; after that it sleeps 20 us at a time, and without requests
+ * until the next.  Lanes run concurrently, so requests
  * that arrive while others run join the device's work as lanes free up,
  * whatever handle they use (two requests for one handle overlap on two
  * lanes); each request completes on its own lane event.  A request's result

@@ -485,8 +485,8 @@ __device__ __forceinline__ bool sc_diagonal_tiled(const DevTable &tab, const Key
 // of a diagonal in term form likewise, with the sign (-1)^{popc(Z & x)}
 // applied by flipping sign bits.  The hi parts are added with Knuth's
 // error-free TwoSum and the lo parts and the TwoSum errors go into a
-// compensation term; a product H * r keeps its rounding error through fma.  The per-sample value s + c is widened to FP64 only
-// when it leaves the lane.
+// compensation term; a product H * r keeps its rounding error through fma.
+// The per-sample value s + c is widened to FP64 only when it leaves the lane.
 
 __device__ __forceinline__ void two_sum(float a, float b, float &s, float &e) {
     s = a + b;

@@ -348,8 +348,9 @@ hipError_t launch_join_pairs(const DevTable &tab, const DevScratch &sc, const ui
 // Batches above this many samples take 64 samples x a block instead of 32:
 // half the operand traffic per pair once that still gives every compute unit
 // four blocks (65,536 spread samples at 100 qubits: 234 us against 358;
-// 37,843 gathered ones at 40 qubits 625 against 682; below it the longer
-// tail costs more, 20,001 gathered ones at 100 qubits 477 against 411).
+// 37,843 gathered ones at 40 qubits 550 against 598, 100,001 at 24 qubits
+// 1,478 against 1,721; below it the longer tail costs more, 20,001 gathered
+// ones at 100 qubits 415 against 352).
 constexpr int64_t kPairsWide = 32768;
 // The comparison of all pairs: scratch, the launch that clears the counters,
 // checks the samples and lays them out, and the pair kernel.

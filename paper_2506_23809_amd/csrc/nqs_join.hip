@@ -15,7 +15,7 @@
 // sums as the other strategies.
 //
 // Grouping without global atomics per entry: the bucket keys are split into
-// partitions by their high bits (about a thousand entries each).  A tile of
+// partitions by their high bits (about two thousand entries each).  A tile of
 // samples counts its entries per partition in LDS and reserves its share
 // of each partition with one atomic; the entries are then placed, each
 // partition is sorted in LDS by (bucket, content fingerprint), and
@@ -412,18 +412,19 @@ __device__ __forceinline__ void join_decide(const DevTable &tab, const DevScratc
     bool chosen = fits && (sc.join_force != 0 || cost < alt);
     if (sc.pairs_rule) {
         // beside the comparison of all pairs (0.09 ps a pair, 0.055 in wide
-        // blocks, and 8 us) the
-        // grouping is spent either way: what counts is the pair kernel, about
-        // two probes a candidate and 18 an entry (11 us for 1.3 M entries at
-        // 100 qubits), and the serial chain of its largest group, 0.1 us a
-        // member of one word and 0.7 us of two.  As matrix tiles a candidate
-        // costs 0.2 probes and an entry 30 (40 qubits, 262,144 spread samples:
-        // 128 us for 1.39 G candidates); a whole probe is counted for the
-        // near pairs, which come up in every block on which they agree, and
-        // 0.01 us a member of the largest group.  A call's time with the
-        // tiles and with all pairs: 53 and 72 us (40 qubits, 9,000 spread
-        // samples), 114 and 136 (37,843 a little gathered ones), 161 and 265
-        // (65,536), 315 and 88 (9,000 gathered ones)
+        // blocks, and 8 us) the grouping is spent either way: what counts is
+        // the pair kernel, about two probes a candidate and 18 an entry (11 us
+        // for 1.3 M entries at 100 qubits), and the serial chain of its
+        // largest group, 0.1 us a member of one word and 0.7 us of two.  As
+        // matrix tiles a candidate costs 0.2 probes and an entry 30 (40
+        // qubits, 262,144 spread samples: 128 us for 1.39 G candidates); a
+        // whole probe is counted for the near pairs, which come up in every
+        // block on which they agree, and 0.01 us a member of the largest
+        // group.  A call's time with the tiles and with all pairs: 53 and 72
+        // us (40 qubits, 9,000 spread samples), 114 and 136 (37,843 a little
+        // gathered ones), 161 and 265 (65,536), 315 and 88 (9,000 gathered
+        // ones).  (A launch of the join alone decides likewise: what it
+        // declines is evaluated again by a launch that holds the comparison.)
         const double dn = static_cast<double>(n);
         const double md = static_cast<double>(m);
         const double pair_cost =

@@ -2151,12 +2151,17 @@ __global__ __launch_bounds__(kFinishMfmaThreads) void eloc_finish_mfma_kernel(
     for (int k = threadIdx.x; k < words; k += blockDim.x) tiles[k] = src[k];
     __syncthreads();
     double d = diag_occ_mfma<W>(tab, x, tiles);
-    if constexpr (SCV)
-        if (!sc_diagonal_tiled<W>(tab, x)) d = sc_diagonal<W>(tab, x);
     // the index again (two registers not held across the diagonal)
     unsigned tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + tid;
+    if constexpr (SCV) {
+        // (the sample again, likewise)
+        if (i < n) {
+            const Key<W> y = load_key<W>(samples, i);
+            if (!sc_diagonal_tiled<W>(tab, y)) d = sc_diagonal<W>(tab, y);
+        }
+    }
     double2 v = make_double2(0.0, 0.0);
     finish_one<W, false, P, false>(tab, sc, samples, n, n_chunks, enum_on != 0, eloc, nullptr,
                                    nullptr, 0, i, nullptr, nullptr, 0, nullptr, nullptr, true, d,
@@ -2605,10 +2610,16 @@ constexpr int64_t kPairsDirect = 8192;
 // streaming.  Picoseconds on MI355X: a pair 0.09 (11.5 us for 8,192 samples
 // at 100 qubits, 5 of them the launch) or 0.055 in wide blocks (234 us for
 // 65,536), a connected pair 30 to 35 against 150 of the enumeration (37,843
-// gathered samples at 40 qubits with 17 M hits: 0.49 ms of kernel; 24 qubits,
-// 100,001 samples, 34 M hits: 1.37 against 7.8), a lookup of the enumeration
-// 0.47 (70.9 ms for 1.5 10^11) and 6 10^7 for the hash it needs, a streamed pair 0.8 beside 1.15 10^8 of
-// its call (20,000 groups past 10,007 samples: 300 us, 500 past 3,619: 172).
+// gathered samples at 40 qubits with 17 M hits: 0.54 ms of kernel; 24 qubits,
+// 100,001 samples, 34 M hits: 1.48 against 7.8), a lookup of the enumeration
+// 0.47 (70.9 ms for 1.5 10^11) and 6 10^7 for the hash it needs, a streamed
+// pair 0.8 beside 1.15 10^8 of its call (20,000 groups past 10,007 samples:
+// 300 us, 500 past 3,619: 172).  Half filling is where a sample has the most
+// lookups, but with few electrons the batches for which they are fewer than
+// the pairs saturate the enumeration's filter (43 batches of one empty spin or
+// 2 to 10 electrons a spin, 120,000 to 2,000,000 samples: all pairs never
+// slower; 100 qubits, 3 + 3, 2,000,000: 228 and 444 ms; the closest, 64
+// qubits, 4 + 4, 2,000,000: 208 and 212).
 // Of a general table nearly every pair may be near, and the group index
 // decides it: 20, or 42 where its buckets are more than 0.4 full and a wave's
 // lookups go on to further ones.  All pairs and streaming, us: 26 qubits, 12

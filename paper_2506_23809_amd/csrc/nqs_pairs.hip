@@ -11,10 +11,10 @@
 // threshold sits in its C operand, and a pair is near where the result is
 // positive.  The order of the qubits does not matter to the product, so the
 // operands are made from the bit strings by a shift and a mask per eight
-// qubits, where they are loaded.  Near pairs (the group index decides whether X = x ^ y is a flip
-// of the table) are queued per wave and evaluated 64 at a time, the few
-// groups with many terms (single excitations) in a queue of their own, so
-// that a wave's lanes run alike.
+// qubits, where they are loaded.  Near pairs (the group index decides whether
+// X = x ^ y is a flip of the table) are queued per wave and evaluated 64 at a
+// time, the few groups with many terms (single excitations) in a queue of
+// their own, so that a wave's lanes run alike.
 //
 // Determinism: each sample's contributions are added as double-doubles (one
 // rounding of a sum whose error is below 2^-100 of its largest partial), so
@@ -107,7 +107,12 @@ struct PairsWave {
 // the operand and 256 bytes W / H of bits from the caches (as finished
 // operands 1 KB, no VALU instructions and no faster: 8,192 samples without a near
 // pair 12.0 and 11.5 us at 40 qubits, 11.7 and 12.6 at 100); per near pair the
-// gathers of its record, group and values.
+// gathers of its record, group and values and the FP64 amplitude ratio.
+// Gathered samples are bound by VALU issue first and those gathers second:
+// 37,843 at 40 qubits (17 M hits) 544 us, of which the VALU instructions take
+// 350, the matrix cores 18, with 75 M requests to L2 (99% hits) and waves
+// waiting 46% of their time; 20,001 at 100 qubits (7.7 M hits) 356 us, VALU
+// 185, waiting 60%.
 // Registers: 128 (four waves a SIMD); at 134 the 100-qubit form took 627 us
 // instead of 508 for 20,001 gathered samples, at 96 it spilled (600).
 template <int W, int H, bool DUMP, int P, bool SCV>
