@@ -1267,6 +1267,11 @@ int nqs_autotune(nqs_ham h, int64_t n, const uint64_t *samples, const double *lo
         if (it != cache.end()) {
             h->tune = nqs::Tuning{it->second.t.threads, it->second.t.filter_bits,
                                   it->second.t.blocks_per_cu, it->second.t.strategy};
+            // (the built-in plan is stored as its defaults spelled out, but its
+            // filter also follows the batch: back to what was timed)
+            const nqs_tuning built_in = filled(nqs::Tuning{0, 0, 0, nqs::kStrategyAuto});
+            if (std::memcmp(&it->second.t, &built_in, sizeof built_in) == 0)
+                h->tune = nqs::Tuning{0, 0, 0, nqs::kStrategyAuto};
             if (best) *best = filled(h->tune);
             if (best_ms) *best_ms = -1.0;
             return NQS_OK;
